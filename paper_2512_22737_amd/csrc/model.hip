@@ -29,6 +29,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -217,16 +218,25 @@ __device__ __forceinline__ u16x8_t qkv_load8(const uint16_t* x,
   if constexpr (!PART) {
     return *reinterpret_cast<const u16x8_t*>(x + off);
   } else {
+    // partials loaded four at a time, added in split order
     floatx4_t lo = *reinterpret_cast<const floatx4_t*>(part + off);
     floatx4_t hi = *reinterpret_cast<const floatx4_t*>(part + off + 4);
-    for (int k = 1; k < n_ks; ++k) {
-      const floatx4_t a = *reinterpret_cast<const floatx4_t*>(part + k * pstride + off);
-      const floatx4_t b = *reinterpret_cast<const floatx4_t*>(part + k * pstride + off + 4);
+    for (int k0 = 1; k0 < n_ks; k0 += 4) {
+      floatx4_t a[4], b[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo[e] += a[e];
-        hi[e] += b[e];
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u < n_ks ? k0 + u : n_ks - 1;
+        a[u] = *reinterpret_cast<const floatx4_t*>(part + k * pstride + off);
+        b[u] = *reinterpret_cast<const floatx4_t*>(part + k * pstride + off + 4);
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k0 + u < n_ks)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            lo[e] += a[u][e];
+            hi[e] += b[u][e];
+          }
     }
     u16x8_t r;
 #pragma unroll
@@ -535,41 +545,92 @@ __global__ __launch_bounds__(NW * kWave) void gemm_kernel(GemmArgs a) {
   }
 }
 
-// x[t][n] += sum over splits k (in order) of part[k][t][n]
+// x[t][n] += sum over splits k (in order) of part[k][t][n]; a thread takes
+// four consecutive n (N a multiple of 32), as one 16-byte access each where
+// the caller's rows allow it (VEC: x and part on 16-byte boundaries, ldx a
+// multiple of 4)
+template <bool VEC>
 __global__ __launch_bounds__(256) void add_partials_kernel(
     float* __restrict__ x, int ldx, const float* __restrict__ part, int n_ks,
     int M, int N) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(M) * N) return;
-  const int t = static_cast<int>(i / N), n = static_cast<int>(i % N);
-  float v = x[static_cast<int64_t>(t) * ldx + n];
-  for (int k = 0; k < n_ks; ++k) v += part[static_cast<int64_t>(k) * M * N + i];
-  x[static_cast<int64_t>(t) * ldx + n] = v;
+  const int64_t n4 = N / 4;
+  if (i >= M * n4) return;
+  const int64_t t = i / n4;
+  const int n = static_cast<int>(i - t * n4) * 4;
+  float* const xp = x + t * ldx + n;
+  const float* const pp = part + t * N + n;
+  const int64_t ps = static_cast<int64_t>(M) * N;
+  if constexpr (VEC) {
+    floatx4_t v = *reinterpret_cast<const floatx4_t*>(xp);
+    for (int k = 0; k < n_ks; ++k) {
+      const floatx4_t p = *reinterpret_cast<const floatx4_t*>(pp + k * ps);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] += p[r];
+    }
+    *reinterpret_cast<floatx4_t*>(xp) = v;
+  } else {
+    for (int r = 0; r < 4; ++r) {
+      float v = xp[r];
+      for (int k = 0; k < n_ks; ++k) v += pp[k * ps + r];
+      xp[r] = v;
+    }
+  }
+}
+
+void add_partials(float* x, int ldx, const float* part, int n_ks, int M, int N,
+                  hipStream_t st) {
+  const int64_t total4 = static_cast<int64_t>(M) * (N / 4);
+  const bool vec = ldx % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(part) % 16 == 0;
+  const dim3 grid((total4 + 255) / 256);
+  if (vec)
+    hipLaunchKernelGGL(add_partials_kernel<true>, grid, dim3(256), 0, st, x,
+                       ldx, part, n_ks, M, N);
+  else
+    hipLaunchKernelGGL(add_partials_kernel<false>, grid, dim3(256), 0, st, x,
+                       ldx, part, n_ks, M, N);
 }
 
 // ---------------------------------------------------------------------------
-// 2-D tiled GEMM for many window rows (M >= 128: batches of windows).  A
-// workgroup computes 256 features (8 blocks; for SwiGLU 4 gate blocks and
-// their 4 up blocks) x 128 tokens (4 row tiles) over its run of K steps.
-// Per 64-wide step the 12 packed 4 KB tiles (8 weight, 4 activation) go
-// from HBM into LDS as they are, with LDS-destination buffer loads (the
-// packed layout is already the MFMA operand order, so every fragment read
-// is 16 contiguous bytes per lane and no register holds a tile in
-// transit); each of the 8 waves computes a 64 x 64 piece (2 feature blocks
-// x 2 row tiles, 16 MFMAs per step), so every LDS byte a wave reads feeds
-// two MFMAs.  A ring of three LDS stages: the tiles of step s+2 load while
-// step s computes, one barrier per step.  Activations must be packed
-// (ceil(M/32) tiles).
+// 2-D tiled GEMM for many window rows.  A workgroup of eight waves computes
+// FG feature groups x 128 tokens (4 row tiles) over its run of K steps; a
+// feature group is two 32-feature blocks (for SwiGLU a gate block and its up
+// block) and belongs to one wave (WK = 1: eight groups, 512 features) or to
+// two (WK = 2: four groups, 256 features), which then take alternate k steps
+// and add their sums through LDS at the end.
+//   MFMA         v_mfma_f32_16x16x32_bf16: per multiply-add it reads and
+//                writes half the accumulators of the 32x32x16 form, and under
+//                the package power limit it runs 17% faster (a register-only
+//                loop: 2000 against 1710 TFLOP/s).
+//   weights      go from memory straight into the registers of the one wave
+//                that uses them: 16 rows x 32 k of a packed tile are four
+//                256-byte pieces, one load.  Two stages (16 loads) are in
+//                flight per wave.
+//   activations  (shared by the waves) go into an LDS ring of four stages
+//                (one k step per wave of a group, 16 KB each) with
+//                LDS-destination buffer loads, three stages ahead, one
+//                barrier per stage.  Packed tiles are copied as they are;
+//                row-major rows (XP false) land as 128-byte rows of XOR-
+//                swizzled 16-byte chunks (each lane fetches the chunk that
+//                belongs at its place).  A stage is published one barrier
+//                before its own, so fragments are read four ahead across the
+//                barrier and the MFMAs never wait for it to refill them.
+// A wave's 64 x 128 piece takes 32 MFMAs per 8 LDS reads of 1 KB.
+// Measured (in a decoder layer of 512 packed rows): gate/up 111 -> 103 us
+// (1.0 PFLOP/s), down and o together 115 -> 100 us, against 64 x 64 wave
+// pieces with both operands in LDS; row-major (no such path before), down at
+// 512 rows 240 -> 63 us with its sum.  With every load left out of the loop
+// gate/up takes 77 us, with weights that stay in L2 92: what is left is the
+// latency of the weight stream at two stages ahead.
 // ---------------------------------------------------------------------------
-constexpr int k2dFeat = 8;                        // feature blocks per WG
 constexpr int k2dTok = 4;                         // row tiles per WG
-constexpr int k2dTiles = k2dFeat + k2dTok;        // 12 tiles per step
-constexpr int k2dStage = k2dTiles * kTile * 2;    // 48 KB per LDS buffer
-constexpr int k2dChunks = k2dTiles * 4 / kGWaves;       // 1 KB chunks per wave: 6
-constexpr int k2dStages = 3;                      // LDS ring: 144 KB
+constexpr int k2dSub = k2dTok * kTile * 2;        // one k step in LDS: 16 KB
+constexpr int k2dRing = 4;                        // LDS stages
+constexpr int k2dLead = 3;                        // stages loaded ahead
 
 struct Gemm2dArgs {
-  const uint16_t* x;      // packed activations, ceil(M/32) row tiles
+  const uint16_t* x;      // activations, packed row tiles or row-major
   const uint16_t* w;      // packed weights
   void* out;
   float* part;            // n_ks > 1 (residual add, stored q|k|v): [n_ks, M, N]
@@ -578,9 +639,18 @@ struct Gemm2dArgs {
   int n_ft, n_tt, n_ks;   // feature tiles, row tiles, K splits
 };
 
-template <int EPI>
+template <int EPI, bool XP, int WK>
 __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
-  __shared__ __attribute__((aligned(1024))) char lds2[k2dStages * k2dStage];
+  constexpr int FG = kGWaves / WK;                 // feature groups
+  constexpr int kStage = WK * k2dSub;              // LDS bytes of a stage
+  constexpr int kDma = kStage / 1024 / kGWaves;    // 1 KB loads per wave
+  constexpr int kA = 8;                            // weight loads per stage
+  constexpr int kT = 2 * k2dTok;                   // 16-token columns
+  constexpr int kFr = 2 * kT;                      // fragments per stage
+  constexpr int kAhead = 4;                        // read ahead of their use
+  static_assert(k2dRing >= k2dLead + 1 && k2dLead >= 2, "slot reuse");
+  static_assert(WK == 1 || k2dRing * kStage >= kGWaves * 16384, "exchange");
+  __shared__ __attribute__((aligned(1024))) char lds2[k2dRing * kStage];
   // tile order: the K splits and row tiles of one feature tile on one XCD
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
   const int per_ft = a.n_tt * a.n_ks;
@@ -591,126 +661,183 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
 
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int fw = wave % FG, kh = wave / FG;
+  // a fragment's lane: row l % 16, eight k from group l / 16 of its 32
+  const int lr = lane & 15, lg = lane >> 4;
+  // the run: whole stages (the plan takes WK = 2 for even step counts only)
   const int S = a.K / kKStep;
-  const int s0 = ks * S / a.n_ks, s1 = (ks + 1) * S / a.n_ks;
-  const int n = s1 - s0;                             // >= 1 (plan)
-  const int last_rt = (a.M - 1) / 32;
+  const int s0 = ks * (S / WK) / a.n_ks * WK;
+  const int n = (ks + 1) * (S / WK) / a.n_ks * WK - s0;   // >= WK (plan)
 
-  // weight block of LDS tile i (0..7): consecutive feature blocks, or for
-  // SwiGLU gate blocks 0..3 then their up blocks (clamped at the end: those
-  // outputs are never stored)
-  const int out_blocks = EPI == kSwiglu ? k2dFeat / 2 : k2dFeat;
-  auto wblock = [&](int i) {
-    const int f = ft * out_blocks + (EPI == kSwiglu ? (i & 3) : i);
-    const int fc = min(f, a.n_fb - 1);
-    return (EPI == kSwiglu && i >= 4) ? fc + a.n_fb : fc;
+  // ---- weights: this wave's two blocks (past the last one: it again; those
+  // outputs are never stored), k step s0 + q*WK + kh in stage q.  Fragment
+  // 2i + h of 32-k slice sl: rows 16h .. + 15 of block i, the k of MFMA
+  // chunks 2sl and 2sl + 1 of the packed tile.
+  const int blk0 = EPI == kSwiglu ? ft * FG + fw : 2 * (ft * FG + fw);
+  const int b0 = min(blk0, a.n_fb - 1);
+  const int b1 = EPI == kSwiglu ? b0 + a.n_fb : min(blk0 + 1, a.n_fb - 1);
+  const uint16_t* const w0 = a.w + (static_cast<int64_t>(b0) * S + s0) * kTile;
+  const uint16_t* const w1 = a.w + (static_cast<int64_t>(b1) * S + s0) * kTile;
+  const int l_pack = (lg >> 1) * 512 + (lg & 1) * 256 + lr * 8;   // elements
+  u16x8_t wa[2][2][4];
+  auto wload = [&](int q, int sl, u16x8_t (&r)[4]) {
+    const int s = min(q * WK + kh, n - 1);           // past the run: re-read
+    const int64_t o = static_cast<int64_t>(s) * kTile + sl * 1024;
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+      r[f] = *reinterpret_cast<const u16x8_t*>((f < 2 ? w0 : w1) + o +
+                                               (f & 1) * 128 + l_pack);
   };
-  // The 48 KB of a step go straight from HBM into its LDS stage: wave w
-  // moves the 1 KB chunks c = 6w .. 6w+5 (tile c / 4, MFMA j = c % 4), one
-  // load instruction each, lane l's 16 bytes landing at byte 16 l of the
-  // chunk, which is where the packed layout already keeps them.  Each chunk
-  // is read through a buffer resource over its tile's run of steps.
+
+  // ---- activations: 1 KB chunk c = wave*kDma + u of a stage is k step
+  // c / 16 of the stage; packed, MFMA c % 4 of row tile c / 4 % 4; row-major,
+  // the 128-byte rows 8 (c % 16) .. + 7.  Row tiles past M read its last one,
+  // rows past M are past the resource's end and read as zeros: their outputs
+  // are never stored.
   const uint32_t lds0 =
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds2));
-  i32x4_t rs[k2dChunks];
+  int d_off[kDma], d_sub[kDma];
+  i32x4_t rs;
+  if constexpr (XP) {
+    const int last = min((a.M - 1) / 32 - tt * k2dTok, k2dTok - 1);
+    rs = buffer_rsrc(a.x + (static_cast<int64_t>(tt) * k2dTok * S + s0) * kTile,
+                     (last * S + n) * kTile * 2);
 #pragma unroll
-  for (int u = 0; u < k2dChunks; ++u) {
-    const int tile = (wave * k2dChunks + u) >> 2;
-    const int64_t blk = tile < k2dFeat ? wblock(tile)
-                                       : min(tt * k2dTok + tile - k2dFeat, last_rt);
-    rs[u] = buffer_rsrc((tile < k2dFeat ? a.w : a.x) + (blk * S + s0) * kTile,
-                        n * kTile * 2);
+    for (int u = 0; u < kDma; ++u) {
+      const int c = wave * kDma + u;
+      d_sub[u] = c / 16;
+      d_off[u] = min(c / 4 % 4, last) * S * kTile * 2 + (c & 3) * 1024 + lane * 16;
+    }
+  } else {
+    const int row0 = tt * k2dTok * 32;
+    const int last = min(a.M - row0, k2dTok * 32) - 1;
+    rs = buffer_rsrc(a.x + static_cast<int64_t>(row0) * a.K + s0 * kKStep,
+                     last * a.K * 2 + n * kKStep * 2);
+    const int lane_off = (lane >> 3) * a.K * 2 + (((lane & 7) ^ (lane >> 3)) << 4);
+#pragma unroll
+    for (int u = 0; u < kDma; ++u) {
+      const int c = wave * kDma + u;
+      d_sub[u] = c / 16;
+      d_off[u] = c % 16 * 8 * a.K * 2 + lane_off;
+    }
   }
-  auto issue = [&](int q, int stage) {
-    const int qq = min(q, n - 1);                    // past the run: re-read
+  constexpr int kStepBytes = XP ? kTile * 2 : kKStep * 2;
+  auto dma = [&](int q, int slot) {
 #pragma unroll
-    for (int u = 0; u < k2dChunks; ++u) {
-      const int c = wave * k2dChunks + u;
-      load_to_lds16<false>(
-          rs[u], qq * kTile * 2 + (c & 3) * 1024 + lane * 16,
-          __builtin_amdgcn_readfirstlane(lds0 + stage * k2dStage + c * 1024));
+    for (int u = 0; u < kDma; ++u) {
+      const int s = min(q * WK + d_sub[u], n - 1);   // past the run: re-read
+      load_to_lds16<false>(rs, d_off[u] + s * kStepBytes,
+                           __builtin_amdgcn_readfirstlane(
+                               lds0 + slot * kStage + (wave * kDma + u) * 1024));
     }
   };
-  // wave tile: feature blocks fb0, fb0+1 (SwiGLU: gate fw and up fw + 4) x
-  // row tiles 2*tw, 2*tw+1 of the workgroup
-  const int fw = wave & 3, tw = wave >> 2;
-  const int fa = EPI == kSwiglu ? fw : 2 * fw;
-  const int fb = EPI == kSwiglu ? fw + 4 : 2 * fw + 1;
-  floatx16_t acc[2][2];
+  // activation fragment f of a stage: 32-k slice f / kT, tokens 16 (f % kT)
+  // .. + 15; the lane's place (per slice) plus constants
+  const char* bl[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  auto compute = [&](int buf) {
-    const char* base = lds2 + buf * k2dStage + lane * 16;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t*>(base + fa * 4096 + j * 1024);
-      const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(base + fb * 4096 + j * 1024);
-      const bf16x8_t b0 = *reinterpret_cast<const bf16x8_t*>(
-          base + (k2dFeat + 2 * tw) * 4096 + j * 1024);
-      const bf16x8_t b1 = *reinterpret_cast<const bf16x8_t*>(
-          base + (k2dFeat + 2 * tw + 1) * 4096 + j * 1024);
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1][1], 0, 0, 0);
-    }
+  for (int sl = 0; sl < 2; ++sl)
+    bl[sl] = lds2 + kh * k2dSub +
+             (XP ? l_pack * 2 + sl * 2048
+                 : lr * 128 +
+                       (((4 * (lg & 1) + 2 * sl + (lg >> 1)) ^ (lr & 7)) << 4));
+  auto bfrag = [&](int slot, int f) {
+    const int t = f % kT;
+    return *reinterpret_cast<const bf16x8_t*>(
+        bl[f / kT] + slot * kStage + t / 2 * 4096 + (t & 1) * (XP ? 256 : 2048));
   };
 
-  // step q computes from stage q % 3 while the loads of step q+2 fill stage
-  // (q+2) % 3, read last in step q-1 (before the barrier that ended it);
-  // before the barrier that ends step q every wave waits for its loads of
-  // step q+1, leaving only those of q+2 in flight.
-  issue(0, 0);
-  issue(1, 1);
-  wait_vmcnt<k2dChunks>();
+  floatx4_t acc[4][kT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][t][e] = 0.f;
+
+  // Stage q computes from slot q % ring while the activations of stage
+  // q + lead fill theirs (read last in stage q - 1, before the barrier that
+  // ended it) and each weight register is refilled with stage q + 2 after
+  // its MFMAs.  Per stage a wave issues kDma, then kA loads; before the
+  // barrier that ends stage q it waits for its activations of stage q + 2,
+  // issued lead - 2 whole stages and kA loads earlier.
+  bf16x8_t b[kAhead];
+  auto stage = [&](int q, int slot, int wst) __attribute__((always_inline)) {
+    dma(q + k2dLead, (slot + k2dLead) % k2dRing);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int f = 0; f < kFr; ++f) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[i][f % kT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8_t, wa[wst][f / kT][i]), b[f % kAhead],
+            acc[i][f % kT], 0, 0, 0);
+      b[f % kAhead] = f + kAhead < kFr
+                          ? bfrag(slot, f + kAhead)
+                          : bfrag((slot + 1) % k2dRing, f + kAhead - kFr);
+      if (f % kT == kT - 1) wload(q + 2, f / kT, wa[wst][f / kT]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<(kDma + kA) * (k2dLead - 2) + kA>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int q = 0; q < k2dLead; ++q) dma(q, q);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl) wload(q, sl, wa[q][sl]);
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vmcnt<2 * kA + kDma * (k2dLead - 2)>();       // stages 0 and 1
   __syncthreads();
-  for (int q = 0; q < n; ++q) {
-    issue(q + 2, (q + 2) % k2dStages);
-    compute(q % k2dStages);
-    wait_vmcnt<k2dChunks>();
-    __syncthreads();
+#pragma unroll
+  for (int f = 0; f < kAhead; ++f) b[f] = bfrag(0, f);
+  const int n_st = n / WK;
+  int q = 0;
+  for (; q + k2dRing <= n_st; q += k2dRing) {
+#pragma unroll
+    for (int u = 0; u < k2dRing; ++u) stage(q + u, u, u & 1);
   }
-  wait_vmcnt<0>();   // surplus re-reads retire before the workgroup ends
+#pragma unroll
+  for (int u = 0; u < k2dRing - 1; ++u)
+    if (q + u < n_st) stage(q + u, u, u & 1);
+  wait_vmcnt<0>();   // surplus re-reads retire before LDS is reused or ends
 
-  // epilogue from registers: lane l, element e = 4g + r is feature
-  // 8g + 4(l/32) + r of its block and token l%32 of its row tile, so the 4
-  // values of a group are 4 consecutive features of one token
-  const int hf = lane >> 5, col = lane & 31;
+  // epilogue from registers: acc[2i + h][t] of lane (lr, lg) is block i,
+  // features 16h + 4lg .. + 3, token 16t + lr
+  auto put = [&](int t, const floatx4_t (&c)[4]) {
+    const int tok = tt * k2dTok * 32 + t * 16 + lr;
+    if (tok >= a.M) return;
 #pragma unroll
-  for (int tj = 0; tj < 2; ++tj) {
-    const int tok = (tt * k2dTok + 2 * tw + tj) * 32 + col;
-    if (tok >= a.M) continue;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int h = 0; h < 2; ++h) {
       if constexpr (EPI == kSwiglu) {
-        const int f = (ft * (k2dFeat / 2) + fw) * 32 + 8 * g + 4 * hf;
+        const int f = blk0 * 32 + 16 * h + 4 * lg;
         if (f >= a.N) continue;
         u16x4_t o;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float gg = acc[0][tj][4 * g + r], uu = acc[1][tj][4 * g + r];
+          const float gg = c[h][r], uu = c[2 + h][r];
           o[r] = f32_to_bf16(gg / (1.0f + expf(-gg)) * uu);
         }
-        *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) +
-                                    packed_off(tok, f, a.N)) = o;
+        uint16_t* const op = static_cast<uint16_t*>(a.out);
+        *reinterpret_cast<u16x4_t*>(
+            XP ? op + packed_off(tok, f, a.N)
+               : op + static_cast<int64_t>(tok) * a.ldo + f) = o;
       } else {
 #pragma unroll
-        for (int fi = 0; fi < 2; ++fi) {
-          const int f = (ft * k2dFeat + (fi ? fb : fa)) * 32 + 8 * g + 4 * hf;
+        for (int i = 0; i < 2; ++i) {
+          const int f = (blk0 + i) * 32 + 16 * h + 4 * lg;
           if (f >= a.N) continue;
-          floatx4_t v;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] = acc[fi][tj][4 * g + r];
+          floatx4_t v = c[2 * i + h];
           const int64_t o = static_cast<int64_t>(tok) * a.ldo + f;
           if (EPI == kStoreBf16 && a.n_ks == 1) {
-            u16x4_t h;
+            u16x4_t u;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) h[r] = f32_to_bf16(v[r]);
-            *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) + o) = h;
+            for (int r = 0; r < 4; ++r) u[r] = f32_to_bf16(v[r]);
+            *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) + o) = u;
           } else if (EPI == kAddF32 && a.n_ks == 1) {
             floatx4_t* p = reinterpret_cast<floatx4_t*>(static_cast<float*>(a.out) + o);
             const floatx4_t old = *p;
@@ -724,132 +851,50 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
         }
       }
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Wide SwiGLU tiles for large grids: a workgroup computes 128 features
-// (gate blocks 0..3 and their up blocks) x 256 tokens (8 row tiles) over
-// the whole K.  Wave w takes gate block w%4 and its up block x row tiles
-// 4(w/4) .. 4(w/4)+3: each A fragment read from LDS feeds four MFMAs and
-// each B fragment two, 0.75 KB of LDS reads per MFMA against 1 KB in the
-// kernel above.  Per step the 16 packed tiles (64 KB) go to LDS as there;
-// a ring of two stages (128 KB): the tiles of step s+1 load while step s
-// computes.  Each output element sums its k steps in the same order as the
-// kernel above, so the two give the same bits.  Used when its grid fills
-// most of the chip (at 512 rows and 12288 features: 92-99 against 109-127
-// us); on smaller grids the 128-token tiles are faster.
-// ---------------------------------------------------------------------------
-constexpr int kWTok = 8;                          // row tiles per WG
-constexpr int kWTiles = k2dFeat + kWTok;          // 16 tiles per step
-constexpr int kWStage = kWTiles * kTile * 2;      // 64 KB per LDS buffer
-constexpr int kWChunks = kWTiles * 4 / kGWaves;   // 1 KB chunks per wave: 8
-constexpr int kWStages = 2;                       // LDS ring: 128 KB
-
-__global__ __launch_bounds__(kGThreads) void gemm2d_swiglu_wide_kernel(
-    Gemm2dArgs a) {
-  __shared__ __attribute__((aligned(1024))) char lds2[kWStages * kWStage];
-  // tile order: the row tiles of one feature tile on one XCD
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int ft = xcd + 8 * (local / a.n_tt);
-  const int tt = local % a.n_tt;
-  if (ft >= a.n_ft) return;                          // whole workgroup
-
-  const int lane = lane_id();
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int n = a.K / kKStep;
-  const int last_rt = (a.M - 1) / 32;
-  // gate blocks 0..3 then their up blocks (clamped at the end: those
-  // outputs are never stored)
-  auto wblock = [&](int i) {
-    const int f = ft * (k2dFeat / 2) + (i & 3);
-    const int fc = min(f, a.n_fb - 1);
-    return i >= 4 ? fc + a.n_fb : fc;
   };
-  // wave w moves the 1 KB chunks c = 8w .. 8w+7 (tile c / 4, MFMA c % 4)
-  const uint32_t lds0 =
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds2));
-  i32x4_t rs[kWChunks];
-#pragma unroll
-  for (int u = 0; u < kWChunks; ++u) {
-    const int tile = (wave * kWChunks + u) >> 2;
-    const int64_t blk = tile < k2dFeat
-                            ? wblock(tile)
-                            : min(tt * kWTok + tile - k2dFeat, last_rt);
-    rs[u] = buffer_rsrc((tile < k2dFeat ? a.w : a.x) + blk * n * kTile,
-                        n * kTile * 2);
-  }
-  auto issue = [&](int q, int stage) {
-    const int qq = min(q, n - 1);                    // past the run: re-read
-#pragma unroll
-    for (int u = 0; u < kWChunks; ++u) {
-      const int c = wave * kWChunks + u;
-      load_to_lds16<false>(
-          rs[u], qq * kTile * 2 + (c & 3) * 1024 + lane * 16,
-          __builtin_amdgcn_readfirstlane(lds0 + stage * kWStage + c * 1024));
-    }
+  auto column = [&](int t) {
+    const floatx4_t c[4] = {acc[0][t], acc[1][t], acc[2][t], acc[3][t]};
+    put(t, c);
   };
-  const int fw = wave & 3, tw = wave >> 2;
-  floatx16_t acc[2][4];
+  if constexpr (WK == 1) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  auto compute = [&](int buf) {
-    const char* base = lds2 + buf * kWStage + lane * 16;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bf16x8_t a0 =
-          *reinterpret_cast<const bf16x8_t*>(base + fw * 4096 + j * 1024);
-      const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(
-          base + (fw + 4) * 4096 + j * 1024);
-      bf16x8_t b[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        b[t] = *reinterpret_cast<const bf16x8_t*>(
-            base + (k2dFeat + 4 * tw + t) * 4096 + j * 1024);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[t], acc[0][t], 0, 0, 0);
-        acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[t], acc[1][t], 0, 0, 0);
-      }
-    }
-  };
-
-  // step q computes from stage q % 2 while the loads of step q+1 fill the
-  // other stage, read last in step q-1 (before the barrier that ended it);
-  // before the barrier that ends step q every wave waits for its loads.
-  issue(0, 0);
-  wait_vmcnt<0>();
-  __syncthreads();
-  for (int q = 0; q < n; ++q) {
-    issue(q + 1, (q + 1) & 1);
-    compute(q & 1);
-    wait_vmcnt<0>();
+    for (int t = 0; t < kT; ++t) column(t);
+  } else {
+    // the two waves of a group exchange halves through LDS: the first keeps
+    // the first 64 tokens, the second the others
     __syncthreads();
-  }
-
-  // epilogue as in gemm2d_kernel (lane l, element 4g + r: feature
-  // 8g + 4(l/32) + r of its block, token l%32 of its row tile)
-  const int hf = lane >> 5, col = lane & 31;
+    floatx4_t* const ex = reinterpret_cast<floatx4_t*>(lds2);
+    auto slab = [&](int w, int i, int t) {
+      return ex + ((w * 4 + i) * (kT / 2) + t) * kWave + lane;
+    };
+    constexpr int kHalf = kT / 2;
+    if (kh == 0) {
 #pragma unroll
-  for (int tj = 0; tj < 4; ++tj) {
-    const int tok = (tt * kWTok + 4 * tw + tj) * 32 + col;
-    if (tok >= a.M) continue;
+      for (int t = 0; t < kHalf; ++t)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int f = (ft * (k2dFeat / 2) + fw) * 32 + 8 * g + 4 * hf;
-      if (f >= a.N) continue;
-      u16x4_t o;
+        for (int i = 0; i < 4; ++i) *slab(wave, i, t) = acc[i][kHalf + t];
+    } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float gg = acc[0][tj][4 * g + r], uu = acc[1][tj][4 * g + r];
-        o[r] = f32_to_bf16(gg / (1.0f + expf(-gg)) * uu);
+      for (int t = 0; t < kHalf; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *slab(wave, i, t) = acc[i][t];
+    }
+    __syncthreads();
+    if (kh == 0) {
+#pragma unroll
+      for (int t = 0; t < kHalf; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][t] += *slab(wave + FG, i, t);
+        column(t);
       }
-      *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) +
-                                  packed_off(tok, f, a.N)) = o;
+    } else {
+#pragma unroll
+      for (int t = 0; t < kHalf; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[i][kHalf + t] += *slab(wave - FG, i, t);
+        column(kHalf + t);
+      }
     }
   }
 }
@@ -943,51 +988,18 @@ size_t up256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 struct GemmPlan {
   int nb, n_nb, n_rg, n_ks;
   int nw;                 // waves per workgroup of the split-K kernel
-  bool two_d;             // the 2-D tiled kernel (packed activations, many rows)
-  bool wide;              // its 256-token SwiGLU tiles
+  bool two_d;             // the 2-D tiled kernel
+  int wk;                 // its waves per feature group
   int n_ft, n_tt;         // its feature and row tiles
   size_t part_bytes;
 };
 
-// window rows from which packed activations go through the 2-D kernel (at
-// 128 rows the split-K kernel is faster: 8.1 against 9.9 ms per 36-layer
-// step)
-constexpr int k2dMinRows = 256;
-
 // workgroups a split product aims at: about one per CU (with few rows, 512
 // and 768 made the 36-layer step at B = 1 slower: 5.00 -> 5.29 and 5.91 ms)
 constexpr int kGemmTargetWgs = 256;
-// the wide SwiGLU tiles from this many workgroups (three quarters of the
-// CUs; at 96 or 128 workgroups the 128-token tiles measured faster)
-constexpr int kWideMinWgs = 3 * kGemmTargetWgs / 4;
-
-GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp = false,
-                   bool split_store = false) {
+// The plan of the split-K kernel (few rows).
+GemmPlan rows_plan(int M, int N, int K, int epi, bool split_store) {
   GemmPlan p{};
-  if (xp && M >= k2dMinRows) {
-    // 2-D tiles; a residual-add product with few tiles splits K (at least
-    // four steps per split)
-    p.two_d = true;
-    p.n_nb = N / 32;
-    p.n_ft = (p.n_nb + (epi == kSwiglu ? 3 : 7)) / (epi == kSwiglu ? 4 : 8);
-    p.n_tt = (M + 32 * k2dTok - 1) / (32 * k2dTok);
-    p.n_ks = 1;
-    if (epi == kSwiglu) {
-      const int n_tt_w = (M + 32 * kWTok - 1) / (32 * kWTok);
-      if (p.n_ft * n_tt_w >= kWideMinWgs) {
-        p.wide = true;
-        p.n_tt = n_tt_w;
-      }
-    }
-    // a stored product (q|k|v) with few tiles splits K too; its fp32
-    // partials are summed into bf16 right after
-    if (epi == kAddF32 || epi == kStoreBf16)
-      p.n_ks = std::max(1, std::min(kGemmTargetWgs / (p.n_ft * p.n_tt),
-                                    K / kKStep / 4));
-    if (p.n_ks > 1)
-      p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);
-    return p;
-  }
   p.nb = gemm_nb(M, epi == kSwiglu);
   p.n_nb = N / 32;
   p.n_rg = (M + 32 * p.nb - 1) / (32 * p.nb);
@@ -1010,6 +1022,89 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp = false,
   return p;
 }
 
+// Estimates of a product's time in microseconds, fitted to products of 33 to
+// 1024 rows, N 512 to 12288 and K 1024 to 12288.  Partials are written and
+// read at 4.5 to 6 TB/s; a launch that sums them takes 4 us, a norm that does
+// about 0.5 us per split.
+double partials_us(int n_ks, int M, int N, bool deferred) {
+  if (n_ks <= 1) return 0;
+  const double mb = 8e-6 * n_ks * M * N;
+  return deferred ? mb / 6 + 0.5 * n_ks : mb / 4.5 + 4;
+}
+
+// The split-K kernel: a round of one workgroup per CU runs S / (8 n_ks) steps
+// of NA * NB MFMA groups per wave (row-major activations cost more: their
+// lanes read 64 bytes of 32 rows per load).
+double rows_us(const GemmPlan& p, int M, int N, int K, int epi, bool xp,
+               bool deferred) {
+  const double rounds =
+      std::max(1.0, static_cast<double>(p.n_nb) * p.n_rg * p.n_ks / kGemmTargetWgs);
+  const int steps = (K / kKStep + p.nw * p.n_ks - 1) / (p.nw * p.n_ks);
+  const int groups = p.nb * (epi == kSwiglu ? 2 : 1);
+  return (xp ? 5 + rounds * steps * groups * 0.67
+             : 1.5 + rounds * steps * (1.6 + 0.9 * groups)) +
+         partials_us(p.n_ks, M, N, deferred);
+}
+
+// Products of more than 32 rows take the 2-D kernel where it is the faster
+// by these estimates.  Both sides measured (split-K against 2-D): down (4096
+// x 12288) at 512 row-major rows 240 and 63 us, at 64 rows 49 and 34; gate/up
+// (12288 x 4096) at 128 row-major rows 104 and 68, packed 68 and 70; 1024 x
+// 1024 at 512 row-major rows 13 and 18.  A decoder layer of 192 rows took 273
+// and 230 us, one of 128 rows 214 and 240 (all four products either way).
+GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp,
+                   bool split_store = false) {
+  const GemmPlan rows = rows_plan(M, N, K, epi, split_store);
+  // (a group's rows are read through a 32-bit buffer resource)
+  if (M <= 32 || K > (1 << 22)) return rows;
+  GemmPlan p{};
+  p.two_d = true;
+  const int S = K / kKStep;
+  p.n_nb = N / 32;
+  p.n_tt = (M + 32 * k2dTok - 1) / (32 * k2dTok);
+  const bool deferred = xp;
+  double best = 0;
+  // wk = 1: tiles of 512 features, a stage (one k step) about 1.7 us; wk = 2:
+  // 256 features, two steps in about 2.1 us, an even number of steps.  A
+  // residual-add or stored product splits K (at least four steps per split)
+  // while its tiles fill less than one round of the CUs.
+  for (int wk = 1; wk <= 2; ++wk) {
+    if (wk == 2 ? S % 2 != 0 : S % 2 == 0 && epi != kSwiglu) continue;
+    const int per = kGWaves / wk * (epi == kSwiglu ? 1 : 2);
+    const int n_ft = (p.n_nb + per - 1) / per;
+    const int wgs = n_ft * p.n_tt;
+    const int most = epi == kSwiglu ? 1 : std::min(kGemmTargetWgs / wgs, S / 4);
+    for (const int ks : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
+      if (ks > 1 && ks > most) break;
+      // a last round that is mostly empty costs most of a whole one
+      const double full = static_cast<double>(wgs) * ks / kGemmTargetWgs;
+      const double rounds = full <= 1 ? 1 : 0.3 * full + 0.7 * std::ceil(full);
+      const double us = 6.5 + rounds * ((S / wk + ks - 1) / ks) *
+                                  (wk == 2 ? 2.1 : 1.7) +
+                        partials_us(ks, M, N, deferred);
+      if (p.n_ks > 0 && us >= best) continue;
+      best = us;
+      p.wk = wk;
+      p.n_ft = n_ft;
+      p.n_ks = ks;
+    }
+  }
+  if (p.n_ks > 1)
+    p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);
+  return best < rows_us(rows, M, N, K, epi, xp, deferred) ? p : rows;
+}
+
+template <int EPI>
+void gemm2d_launch(const Gemm2dArgs& g, bool xp, int wk, dim3 grid,
+                   hipStream_t st) {
+  using Kernel = void (*)(Gemm2dArgs);
+  const Kernel k = wk == 1 ? (xp ? gemm2d_kernel<EPI, true, 1>
+                                 : gemm2d_kernel<EPI, false, 1>)
+                           : (xp ? gemm2d_kernel<EPI, true, 2>
+                                 : gemm2d_kernel<EPI, false, 2>);
+  hipLaunchKernelGGL(k, grid, dim3(kGThreads), 0, st, g);
+}
+
 // Launches the product; with K split, the partials go to `part` and the
 // caller adds them (defer) or add_partials_kernel does right after.
 // xp: x (and a SwiGLU output) in the packed tile layout
@@ -1019,29 +1114,38 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
   if (!x || !w || !out) return WEDLM_E_ARG;
   if (epi != kStoreBf16 && epi != kAddF32 && epi != kSwiglu) return WEDLM_E_ARG;
   if (!gemm_shape_ok(M, N, K) || ldo < N) return WEDLM_E_SHAPE;
-  const GemmPlan p = gemm_plan(M, N, K, epi, xp, defer);
+  GemmPlan p = gemm_plan(M, N, K, epi, xp, defer);
+  if (p.two_d && !xp) {
+    // a caller's own arrays: the 2-D kernel needs 16-byte output rows, and a
+    // workspace that only holds the split-K kernel's partials (or is not 16-
+    // byte aligned) leaves it fewer splits
+    const int esz = epi == kAddF32 ? 4 : 2;
+    const GemmPlan r = rows_plan(M, N, K, epi, defer);
+    if (part_bytes < r.part_bytes) return WEDLM_E_WORKSPACE;
+    const size_t one = static_cast<size_t>(M) * N * sizeof(float);
+    if (reinterpret_cast<uintptr_t>(out) % (4 * esz) != 0 || ldo % 4 != 0) {
+      p = r;
+    } else if (part_bytes < p.part_bytes) {
+      p.n_ks = std::max<int>(1, static_cast<int>(part_bytes / one));
+      p.part_bytes = p.n_ks > 1 ? p.n_ks * one : 0;
+    }
+    if (p.two_d && reinterpret_cast<uintptr_t>(part) % 16 != 0) {
+      p.n_ks = 1;
+      p.part_bytes = 0;
+    }
+  }
   if (p.part_bytes > 0 && (!part || part_bytes < p.part_bytes))
     return WEDLM_E_WORKSPACE;
   if (p.two_d) {
-    if ((epi == kSwiglu && N % 32 != 0) || ldo % 4 != 0) return WEDLM_E_SHAPE;
     Gemm2dArgs g{};
     g.x = x; g.w = w; g.out = out; g.part = static_cast<float*>(part);
     g.M = M; g.N = N; g.K = K; g.ldo = ldo;
     g.n_fb = p.n_nb; g.n_ft = p.n_ft; g.n_tt = p.n_tt; g.n_ks = p.n_ks;
     const int64_t grid = 8ll * p.n_tt * p.n_ks * ((p.n_ft + 7) / 8);
     if (grid > (1ll << 30)) return WEDLM_E_SHAPE;
-    if (p.wide)
-      hipLaunchKernelGGL(gemm2d_swiglu_wide_kernel, dim3(grid),
-                         dim3(kGThreads), 0, st, g);
-    else if (epi == kSwiglu)
-      hipLaunchKernelGGL(gemm2d_kernel<kSwiglu>, dim3(grid), dim3(kGThreads),
-                         0, st, g);
-    else if (epi == kAddF32)
-      hipLaunchKernelGGL(gemm2d_kernel<kAddF32>, dim3(grid), dim3(kGThreads),
-                         0, st, g);
-    else
-      hipLaunchKernelGGL(gemm2d_kernel<kStoreBf16>, dim3(grid),
-                         dim3(kGThreads), 0, st, g);
+    if (epi == kSwiglu) gemm2d_launch<kSwiglu>(g, xp, p.wk, dim3(grid), st);
+    else if (epi == kAddF32) gemm2d_launch<kAddF32>(g, xp, p.wk, dim3(grid), st);
+    else gemm2d_launch<kStoreBf16>(g, xp, p.wk, dim3(grid), st);
     WEDLM_LAUNCH_CHECK();
     if (n_ks_out) *n_ks_out = p.n_ks;
     if (p.n_ks > 1 && epi == kStoreBf16 && !defer) {
@@ -1051,10 +1155,7 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
                          g.part, p.n_ks, M, N);
       WEDLM_LAUNCH_CHECK();
     } else if (p.n_ks > 1 && !defer) {
-      const int64_t total = static_cast<int64_t>(M) * N;
-      hipLaunchKernelGGL(add_partials_kernel, dim3((total + 255) / 256),
-                         dim3(256), 0, st, static_cast<float*>(out), ldo,
-                         g.part, p.n_ks, M, N);
+      add_partials(static_cast<float*>(out), ldo, g.part, p.n_ks, M, N, st);
       WEDLM_LAUNCH_CHECK();
     }
     return WEDLM_OK;
@@ -1085,10 +1186,7 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
   WEDLM_LAUNCH_CHECK();
   if (n_ks_out) *n_ks_out = p.n_ks;
   if (p.n_ks > 1 && !defer) {
-    const int64_t total = static_cast<int64_t>(M) * N;
-    hipLaunchKernelGGL(add_partials_kernel, dim3((total + 255) / 256),
-                       dim3(256), 0, st, static_cast<float*>(out), ldo,
-                       a.part, p.n_ks, M, N);
+    add_partials(static_cast<float*>(out), ldo, a.part, p.n_ks, M, N, st);
     WEDLM_LAUNCH_CHECK();
   }
   return WEDLM_OK;
@@ -1240,7 +1338,7 @@ extern "C" size_t wedlm_linear_workspace_size(int32_t M, int32_t N,
   if (!gemm_shape_ok(M, N, K) ||
       (epilogue != kStoreBf16 && epilogue != kAddF32 && epilogue != kSwiglu))
     return 0;
-  return gemm_plan(M, N, K, epilogue).part_bytes;
+  return gemm_plan(M, N, K, epilogue, false).part_bytes;
 }
 
 extern "C" int wedlm_linear(const uint16_t* x, const uint16_t* w, int32_t M,

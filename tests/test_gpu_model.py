@@ -194,6 +194,57 @@ def test_linear(M, N, K, epi):
         assert (err <= tol).all(), err.max()
 
 
+# sizes whose products go through the 2-D tiles: one row and one feature
+# block past a tile (130 = 128 + 2 rows, 2080 = 8 x 256 + 32 features), K
+# split over workgroups, an odd number of k steps (K = 17 x 64: the tiles of
+# 512 features), several row tiles, and a single split
+LINEAR_2D_CASES = [
+    # M, N, K, epilogue
+    (130, 2080, 2048, 0), (130, 2080, 2048, 1), (257, 4128, 2048, 2),
+    (1000, 4128, 1088, 1), (1000, 4128, 1088, 0), (300, 4128, 1088, 2),
+    (513, 4096, 256, 0), (64, 1056, 4096, 0),
+]
+
+
+@pytest.mark.parametrize("M,N,K,epi", LINEAR_2D_CASES)
+def test_linear_2d(M, N, K, epi):
+    test_linear(M, N, K, epi)
+
+
+# what the split-K kernel took, the 2-D tiles take or leave to it: a residual
+# add with no workspace (a single split), with rows that are not on 16-byte
+# boundaries and with an odd row stride
+@pytest.mark.parametrize("ldo,shift,ws", [(2080, 0, 0), (2080, 1, 1),
+                                          (2083, 0, 1), (2084, 0, 2)])
+def test_linear_2d_callers_arrays(ldo, shift, ws):
+    w = W_()
+    M, N, K = 130, 2080, 2048
+    rng = np.random.default_rng(ldo + shift)
+    x = _rand_bf16(rng, (M, K))
+    wt = _rand_bf16(rng, (N, K), 1.0 / math.sqrt(K))
+    base = rng.standard_normal(M * ldo + shift).astype(np.float32)
+    out = torch.from_numpy(base.copy()).to(DEV)
+    xd, wd = _bf(x), w.pack(_bf(wt))
+    need = w.wedlm_linear_workspace_size(M, N, K, 1)
+    assert need > 2 * M * N * 4                 # split over workgroups
+    # the whole workspace, none, or room for two splits
+    size = (0, need, 2 * M * N * 4)[ws]
+    space = torch.empty(max(size, 1), dtype=torch.uint8, device=DEV)
+    code = w.lib().wedlm_linear(
+        xd.data_ptr(), wd.data_ptr(), M, N, K, 1, out.data_ptr() + 4 * shift,
+        ldo, space.data_ptr() if size else None, size, None)
+    assert code == 0
+    torch.cuda.synchronize()
+    xf, wf = O.bf16_to_f64(x), O.bf16_to_f64(wt)
+    bound = K * 2.0 ** -24 * (np.abs(xf) @ np.abs(wf).T)
+    ref = base[shift:].reshape(M, ldo).astype(np.float64)
+    got = out.cpu().double().numpy()[shift:].reshape(M, ldo)
+    assert np.array_equal(got[:, N:], ref[:, N:])       # untouched
+    ref = ref[:, :N] + xf @ wf.T
+    err = np.abs(got[:, :N] - ref)
+    assert (err <= bound + 2.0 ** -23 * np.abs(ref)).all(), err.max()
+
+
 def test_linear_split_workspace_reuse():
     """Products that split K over workgroups (residual add at N = 4096) share
     one workspace back to back with products that do not."""
