@@ -639,6 +639,14 @@ struct Gemm2dArgs {
   int n_ft, n_tt, n_ks;   // feature tiles, row tiles, K splits
 };
 
+// XOR swizzle of the 16-byte chunks of a row-major LDS row (128 bytes): the
+// lanes that one pass of ds_read_b128 serves together (0-3, 12-15, 20-23,
+// 24-27, ...) then read 16 different chunks of 256 bytes (r & 7 left half of
+// the passes on the same chunks).
+__device__ __forceinline__ int x_swz(int r) {
+  return ((r >> 1) & 1) | ((r >> 2) & 2);
+}
+
 template <int EPI, bool XP, int WK>
 __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
   constexpr int FG = kGWaves / WK;                 // feature groups
@@ -691,9 +699,9 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
 
   // ---- activations: 1 KB chunk c = wave*kDma + u of a stage is k step
   // c / 16 of the stage; packed, MFMA c % 4 of row tile c / 4 % 4; row-major,
-  // the 128-byte rows 8 (c % 16) .. + 7.  Row tiles past M read its last one,
-  // rows past M are past the resource's end and read as zeros: their outputs
-  // are never stored.
+  // the 128-byte rows 8 (c % 16) .. + 7.  Rows past M read its last row (or
+  // tile): their outputs are never stored, but every load reads memory, since
+  // one wholly out of a resource's range is counted done ahead of older ones.
   const uint32_t lds0 =
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds2));
   int d_off[kDma], d_sub[kDma];
@@ -713,12 +721,12 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
     const int last = min(a.M - row0, k2dTok * 32) - 1;
     rs = buffer_rsrc(a.x + static_cast<int64_t>(row0) * a.K + s0 * kKStep,
                      last * a.K * 2 + n * kKStep * 2);
-    const int lane_off = (lane >> 3) * a.K * 2 + (((lane & 7) ^ (lane >> 3)) << 4);
 #pragma unroll
     for (int u = 0; u < kDma; ++u) {
       const int c = wave * kDma + u;
       d_sub[u] = c / 16;
-      d_off[u] = c % 16 * 8 * a.K * 2 + lane_off;
+      const int r = c % 16 * 8 + (lane >> 3);
+      d_off[u] = min(r, last) * a.K * 2 + (((lane & 7) ^ x_swz(r)) << 4);
     }
   }
   constexpr int kStepBytes = XP ? kTile * 2 : kKStep * 2;
@@ -739,7 +747,7 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
     bl[sl] = lds2 + kh * k2dSub +
              (XP ? l_pack * 2 + sl * 2048
                  : lr * 128 +
-                       (((4 * (lg & 1) + 2 * sl + (lg >> 1)) ^ (lr & 7)) << 4));
+                       (((4 * (lg & 1) + 2 * sl + (lg >> 1)) ^ x_swz(lr)) << 4));
   auto bfrag = [&](int slot, int f) {
     const int t = f % kT;
     return *reinterpret_cast<const bf16x8_t*>(
