@@ -545,6 +545,102 @@ __global__ __launch_bounds__(NW * kWave) void gemm_kernel(GemmArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Up to 32 rows, K 4096 or 2048 and more feature blocks (for SwiGLU gate
+// blocks with their up blocks) than CUs: a persistent form of the kernel
+// above.  A workgroup loads its waves' activations once (SPW steps per wave,
+// 128 registers at 8) and walks several blocks; the weight loads run two steps
+// ahead across blocks, so the stream never stops for a block's sum, and the
+// activations are read from L2 once per workgroup instead of once per block
+// (row-major ones 64 bytes of 32 rows at a time).  The waves' sums of a block
+// meet in one of two LDS buffers, in wave order, with one barrier per block:
+// the same bits as the plain form.  Bound by the weight stream: gate/up (201
+// MB) at 32 row-major rows 50 -> 41 us, at 16 43 -> 38, at one 39 -> 36; a
+// decoder step of one window, 8 layers, 1236 -> 1197 us with packed ones.
+// (K split three ways, down at one row took 23 us against 21.)
+// ---------------------------------------------------------------------------
+template <int NA, int SPW, int EPI, bool XP>
+__global__ __launch_bounds__(kGThreads) void gemm_persistent_kernel(
+    GemmArgs a) {
+  constexpr int PF = 2;
+  static_assert(SPW % PF == 0, "stages line up with blocks");
+  __shared__ float red[2][kGWaves * NA * 32 * kRedStride];
+  const int g = blockIdx.x, per = gridDim.x;
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int col = lane & 31, hf = lane >> 5;
+  const int S = a.K / kKStep;
+  const int s0 = wave * SPW;                         // this wave's k steps
+  const int n_it = (a.n_nb - g + per - 1) / per;     // >= 1 (plan)
+
+  u16x8_t xb[SPW][4];
+#pragma unroll
+  for (int s = 0; s < SPW; ++s)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      xb[s][u] = *reinterpret_cast<const u16x8_t*>(
+          XP ? a.x + (static_cast<int64_t>(s0 + s) * 4 + u) * 512 + lane * 8
+             : a.x + static_cast<int64_t>(min(col, a.M - 1)) * a.K + hf * 32 +
+                   (s0 + s) * kKStep + u * 8);
+
+  u16x8_t wa[PF][NA][4];
+  auto load = [&](int it, int s, u16x8_t (&r)[NA][4]) {
+    const int nb = g + min(it, n_it - 1) * per;      // past the run: re-read
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const uint16_t* const p =
+          a.w + (static_cast<int64_t>(nb + i * a.up_blk) * S + s0 + s) * kTile;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        r[i][u] = __builtin_nontemporal_load(
+            reinterpret_cast<const u16x8_t*>(p + u * 512 + lane * 8));
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < PF; ++p) load(0, p, wa[p]);
+
+  for (int it = 0; it < n_it; ++it) {
+    floatx16_t acc[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[i] = floatx16_t{};
+#pragma unroll
+    for (int s = 0; s < SPW; ++s) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8_t, wa[s % PF][i][j]),
+              __builtin_bit_cast(bf16x8_t, xb[s][j]), acc[i], 0, 0, 0);
+      if (s + PF < SPW) load(it, s + PF, wa[s % PF]);
+      else load(it + 1, s + PF - SPW, wa[s % PF]);
+    }
+    float* const rb = red[it & 1];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        rb[((wave * NA + i) * 32 + 8 * (e >> 2) + 4 * hf + (e & 3)) * kRedStride +
+           col] = acc[i][e];
+    __syncthreads();
+    // thread -> (feature, token), 32 x 16 per pass
+    const int nb = g + it * per, f = threadIdx.x & 31;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int tok = (threadIdx.x >> 5) + 16 * half;
+      float v[NA];
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        v[i] = 0.f;
+#pragma unroll
+        for (int w = 0; w < kGWaves; ++w)
+          v[i] += rb[((w * NA + i) * 32 + f) * kRedStride + tok];
+      }
+      if (tok < a.M) gemm_store<EPI, XP>(a, tok, nb * 32 + f, v[0], v[NA - 1]);
+    }
+  }
+}
+
 // x[t][n] += sum over splits k (in order) of part[k][t][n]; a thread takes
 // four consecutive n (N a multiple of 32), as one 16-byte access each where
 // the caller's rows allow it (VEC: x and part on 16-byte boundaries, ldx a
@@ -996,6 +1092,8 @@ size_t up256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 struct GemmPlan {
   int nb, n_nb, n_rg, n_ks;
   int nw;                 // waves per workgroup of the split-K kernel
+  int spw, wgs;           // spw > 0: its persistent form, steps per wave and
+                          // workgroups
   bool two_d;             // the 2-D tiled kernel
   int wk;                 // its waves per feature group
   int n_ft, n_tt;         // its feature and row tiles
@@ -1025,9 +1123,30 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool split_store) {
     const int wgs = p.n_nb * p.n_rg;
     p.n_ks = std::max(1, std::min(kGemmTargetWgs / wgs, K / kKStep / kGWaves));
   }
+  // the persistent form: the blocks in as few rounds as of one workgroup per
+  // CU, each workgroup taking the same number of them
+  const int spw = K / kKStep / kGWaves;
+  if (p.nb == 1 && p.n_nb > kGemmTargetWgs && K % (kKStep * kGWaves) == 0 &&
+      (spw == 8 || spw == 4)) {
+    const int rounds = (p.n_nb + kGemmTargetWgs - 1) / kGemmTargetWgs;
+    p.spw = spw;
+    p.nw = kGWaves;
+    p.n_ks = 1;
+    p.wgs = (p.n_nb + rounds - 1) / rounds;
+  }
   if (p.n_ks > 1)
     p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);
   return p;
+}
+
+template <int SPW, bool XP>
+void persistent_launch(const GemmArgs& a, int epi, int wgs, hipStream_t st) {
+  using Kernel = void (*)(GemmArgs);
+  const Kernel k =
+      epi == kSwiglu   ? gemm_persistent_kernel<2, SPW, kSwiglu, XP>
+      : epi == kAddF32 ? gemm_persistent_kernel<1, SPW, kAddF32, XP>
+                       : gemm_persistent_kernel<1, SPW, kStoreBf16, XP>;
+  hipLaunchKernelGGL(k, dim3(wgs), dim3(kGThreads), 0, st, a);
 }
 
 // Estimates of a product's time in microseconds, fitted to products of 33 to
@@ -1178,7 +1297,12 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
   if (8ll * a.n_rg * a.n_ks * ((a.n_nb + 7) / 8) > (1ll << 30))
     return WEDLM_E_SHAPE;
   const int nb = p.nb;
-  if (epi == kSwiglu) {
+  if (p.spw > 0) {
+    if (p.spw == 8 && xp) persistent_launch<8, true>(a, epi, p.wgs, st);
+    else if (p.spw == 8) persistent_launch<8, false>(a, epi, p.wgs, st);
+    else if (xp) persistent_launch<4, true>(a, epi, p.wgs, st);
+    else persistent_launch<4, false>(a, epi, p.wgs, st);
+  } else if (epi == kSwiglu) {
     if (nb == 1) gemm_launch<1, 2, 2, kSwiglu>(a, xp, st);
     else gemm_launch<2, 2, 2, kSwiglu>(a, xp, st);
   } else if (epi == kAddF32) {

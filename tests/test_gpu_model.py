@@ -211,6 +211,16 @@ def test_linear_2d(M, N, K, epi):
     test_linear(M, N, K, epi)
 
 
+# the persistent form of up to 32 rows: more 32-feature blocks than CUs (257:
+# one workgroup with a block fewer than the others; 520: three rounds), four
+# and eight steps per wave, one row, a ragged and a full row block
+@pytest.mark.parametrize("M,N,K,epi", [
+    (1, 257 * 32, 2048, 2), (32, 257 * 32, 4096, 2), (31, 520 * 32, 2048, 1),
+    (17, 300 * 32, 4096, 0)])
+def test_linear_persistent(M, N, K, epi):
+    test_linear(M, N, K, epi)
+
+
 # what the split-K kernel took, the 2-D tiles take or leave to it: a residual
 # add with no workspace (a single split), with rows that are not on 16-byte
 # boundaries and with an odd row stride
