@@ -138,27 +138,37 @@ def _check(code: int, what: str):
 
 
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
+_I32, _F32, _U8 = (torch.int32,), (torch.float32,), (torch.uint8,)
 
 
 def _t(x: Optional[torch.Tensor], name: str, dtypes, shape=None,
        allow_none=False):
+    """Address of a checked tensor.  A call checks about 15 of them, so the
+    usual case is one expression; _bad_tensor() finds out what is wrong."""
     if x is None:
         if allow_none:
             return None
         raise WedlmError(f"{name} is required")
+    if (x.dtype in dtypes and x.is_cuda and x.is_contiguous() and
+            (shape is None or x.shape == shape)):
+        return x.data_ptr()
+    _bad_tensor(x, name, dtypes, shape)
+
+
+def _bad_tensor(x, name, dtypes, shape):
     if not x.is_cuda:
         raise WedlmError(f"{name} must be a device tensor")
     if x.dtype not in dtypes:
         raise WedlmError(f"{name}: dtype {x.dtype} not in {dtypes}")
     if not x.is_contiguous():
         raise WedlmError(f"{name} must be contiguous")
-    if shape is not None and tuple(x.shape) != tuple(shape):
-        raise WedlmError(f"{name}: shape {tuple(x.shape)} != {tuple(shape)}")
-    return x.data_ptr()
+    raise WedlmError(f"{name}: shape {tuple(x.shape)} != {tuple(shape)}")
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device (without building the Stream
+    object that torch.cuda.current_stream() returns)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def wedlm_version() -> int:
@@ -177,7 +187,7 @@ def wedlm_reorder(win_tok, win_start, qkv_in, Hq: int, Hkv: int,
     B, W = win_tok.shape
     none = qkv_in is None
     D = (D or 128) if none else qkv_in.shape[-1]
-    i32 = (torch.int32,)
+    i32 = _I32
     code = _load().wedlm_reorder(
         _t(win_tok, "win_tok", i32, (B, W)),
         _t(win_start, "win_start", i32, (B,)),
@@ -207,17 +217,17 @@ def wedlm_window_attn(q_phys, k_phys, v_phys, k_cache, v_cache, block_table,
     maxp = block_table.shape[1]
     if softmax_scale is None:
         softmax_scale = 1.0 / math.sqrt(D)
-    ws_need = wedlm_window_attn_workspace_size(B, W, Hq, Hkv, D,
-                                               max_prefix_len)
     ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
+    if workspace is not None:      # its size is checked by the library
         if not workspace.is_cuda or not workspace.is_contiguous():
             raise WedlmError("workspace must be a contiguous device tensor")
-        ws_ptr = workspace.data_ptr()
-        ws_bytes = workspace.numel() * workspace.element_size()
-    elif ws_need:
-        raise WedlmError(f"workspace of {ws_need} bytes required")
-    i32 = (torch.int32,)
+        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.nbytes
+    else:
+        need = wedlm_window_attn_workspace_size(B, W, Hq, Hkv, D,
+                                                max_prefix_len)
+        if need:
+            raise WedlmError(f"workspace of {need} bytes required")
+    i32 = _I32
     code = _load().wedlm_window_attn(
         _t(q_phys, "q_phys", _BF16), _t(k_phys, "k_phys", _BF16, (B, W, Hkv, D)),
         _t(v_phys, "v_phys", _BF16, (B, W, Hkv, D)),
@@ -227,7 +237,7 @@ def wedlm_window_attn(q_phys, k_phys, v_phys, k_cache, v_cache, block_table,
         _t(prefix_len, "prefix_len", i32, (B,)), B, W, Hq, Hkv, D,
         int(max_prefix_len), float(softmax_scale),
         _t(out, "out", _BF16, (B, W, Hq, D)),
-        _t(lse, "lse", (torch.float32,), (B, W, Hq), allow_none=True),
+        _t(lse, "lse", _F32, (B, W, Hq), allow_none=True),
         _t(status, "status", i32, (B,), allow_none=True), ws_ptr, ws_bytes,
         _stream())
     _check(code, "wedlm_window_attn")
@@ -245,7 +255,7 @@ def wedlm_window_attn_noalloc(q_phys, k_phys, v_phys, k_cache, v_cache,
     maxp = block_table.shape[1]
     if softmax_scale is None:
         softmax_scale = 1.0 / math.sqrt(D)
-    i32 = (torch.int32,)
+    i32 = _I32
     code = _load().wedlm_window_attn_noalloc(
         _t(q_phys, "q_phys", _BF16), _t(k_phys, "k_phys", _BF16, (B, W, Hkv, D)),
         _t(v_phys, "v_phys", _BF16, (B, W, Hkv, D)),
@@ -255,7 +265,7 @@ def wedlm_window_attn_noalloc(q_phys, k_phys, v_phys, k_cache, v_cache,
         _t(prefix_len, "prefix_len", i32, (B,)), B, W, Hq, Hkv, D,
         int(max_prefix_len), float(softmax_scale),
         _t(out, "out", _BF16, (B, W, Hq, D)),
-        _t(lse, "lse", (torch.float32,), (B, W, Hq), allow_none=True),
+        _t(lse, "lse", _F32, (B, W, Hq), allow_none=True),
         _t(status, "status", i32, (B,), allow_none=True), _stream())
     _check(code, "wedlm_window_attn_noalloc")
 
@@ -270,14 +280,14 @@ def wedlm_score(logits, n_obs, temperature: float, argmax, entropy,
     last dimension."""
     B, W, stride = logits.shape
     V = stride if V is None else V
-    need = wedlm_score_workspace_size(B, W, V)
     ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        ws_ptr = workspace.data_ptr()
-        ws_bytes = workspace.numel() * workspace.element_size()
-    elif need:
-        raise WedlmError(f"workspace of {need} bytes required")
-    i32, f32 = (torch.int32,), (torch.float32,)
+    if workspace is not None:      # its size is checked by the library
+        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.nbytes
+    else:
+        need = wedlm_score_workspace_size(B, W, V)
+        if need:
+            raise WedlmError(f"workspace of {need} bytes required")
+    i32, f32 = _I32, _F32
     code = _load().wedlm_score(
         _t(logits, "logits", f32), stride, _t(n_obs, "n_obs", i32, (B,)),
         B, W, V, float(temperature), _t(argmax, "argmax", i32, (B, W)),
@@ -308,8 +318,8 @@ def wedlm_lm_head_score(hidden, w_vocab, temperature: float, argmax, entropy,
         _t(hidden, "hidden", _BF16, (R, Hd)),
         _t(w_vocab, "w_vocab", _BF16, (V, Hd)), R, Hd, V, float(temperature),
         _t(argmax, "argmax", (torch.int32,), (R,)),
-        _t(entropy, "entropy", (torch.float32,), (R,)),
-        _t(pmax, "pmax", (torch.float32,), (R,), allow_none=True),
+        _t(entropy, "entropy", _F32, (R,)),
+        _t(pmax, "pmax", _F32, (R,), allow_none=True),
         ws_ptr, ws_bytes, _stream())
     _check(code, "wedlm_lm_head_score")
 
@@ -321,11 +331,11 @@ def _commit_args(win_tok, win_start, argmax, entropy, tau, lam, k_phys,
     Hkv, D = k_phys.shape[2], k_phys.shape[3]
     P = k_cache.shape[0]
     maxp = block_table.shape[1]
-    i32 = (torch.int32,)
+    i32 = _I32
     return [
         _t(win_tok, "win_tok", i32, (B, W)), _t(win_start, "win_start", i32, (B,)),
         _t(argmax, "argmax", i32, (B, W)),
-        _t(entropy, "entropy", (torch.float32,), (B, W)), float(tau),
+        _t(entropy, "entropy", _F32, (B, W)), float(tau),
         float(lam), _t(k_phys, "k_phys", _BF16, (B, W, Hkv, D)),
         _t(v_phys, "v_phys", _BF16, (B, W, Hkv, D)),
         _t(k_cache, "k_cache", _BF16, (P, Hkv, PAGE_SIZE, D)),
@@ -334,7 +344,7 @@ def _commit_args(win_tok, win_start, argmax, entropy, tau, lam, k_phys,
         _t(n_commit, "n_commit", i32, (B,)),
         _t(committed_tok, "committed_tok", i32, (B, W)),
         _t(committed_slot, "committed_slot", i32, (B, W)),
-        _t(selected, "selected", (torch.uint8,), (B, W)),
+        _t(selected, "selected", _U8, (B, W)),
         _t(status, "status", i32, (B,))]
 
 
@@ -494,14 +504,14 @@ def wedlm_embed(tok, mask_token: int, table, x) -> None:
     code = _load().wedlm_embed(
         _t(tok, "tok", (torch.int32,)), M, int(mask_token),
         _t(table, "table", _BF16), V, Hd,
-        _t(x, "x", (torch.float32,), (M, Hd)), _stream())
+        _t(x, "x", _F32, (M, Hd)), _stream())
     _check(code, "wedlm_embed")
 
 
 def wedlm_rmsnorm(x, gain, eps: float, y) -> None:
     M, Hd = x.shape
     code = _load().wedlm_rmsnorm(
-        _t(x, "x", (torch.float32,)), _t(gain, "gain", _BF16, (Hd,)), M, Hd,
+        _t(x, "x", _F32), _t(gain, "gain", _BF16, (Hd,)), M, Hd,
         float(eps), _t(y, "y", _BF16, (M, Hd)), _stream())
     _check(code, "wedlm_rmsnorm")
 
@@ -542,7 +552,7 @@ def wedlm_linear(x, w, epilogue: int, out, workspace=None) -> None:
     M, K = x.shape
     rows = w.shape[0]
     N = rows // 2 if epilogue == EPI_SWIGLU else rows
-    odt = (torch.float32,) if epilogue == EPI_ADD_F32 else _BF16
+    odt = _F32 if epilogue == EPI_ADD_F32 else _BF16
     if out.dim() != 2 or out.shape[0] != M:
         raise WedlmError(f"out: shape {tuple(out.shape)} is not [{M}, >= {N}]")
     need = wedlm_linear_workspace_size(M, N, K, epilogue)
@@ -561,7 +571,7 @@ def wedlm_qk_norm_rope(qkv, q_gain, k_gain, pos_ids, Hq: int, Hkv: int,
                        v_out) -> None:
     M = qkv.shape[0]
     D = q_gain.shape[0]
-    i32 = (torch.int32,)
+    i32 = _I32
     code = _load().wedlm_qk_norm_rope(
         _t(qkv, "qkv", _BF16, (M, (Hq + 2 * Hkv) * D)),
         _t(q_gain, "q_gain", _BF16, (D,)), _t(k_gain, "k_gain", _BF16, (D,)),
@@ -586,7 +596,7 @@ def wedlm_model_forward(cfg: ModelConfig, weights: ModelWeights, win_tok,
     L, Hkv, D = cfg.n_layers, cfg.n_kv_heads, cfg.head_dim
     P = k_cache.shape[1]
     maxp = block_table.shape[1]
-    i32, f32 = (torch.int32,), (torch.float32,)
+    i32, f32 = _I32, _F32
     code = _load().wedlm_model_forward(
         ctypes.byref(cfg), ctypes.byref(weights),
         _t(win_tok, "win_tok", i32, (B, W)),
@@ -602,7 +612,7 @@ def wedlm_model_forward(cfg: ModelConfig, weights: ModelWeights, win_tok,
         _t(argmax, "argmax", i32, (B, W)), _t(entropy, "entropy", f32, (B, W)),
         _t(pmax, "pmax", f32, (B, W), allow_none=True),
         _t(status, "status", i32, (B,)), _t(workspace, "workspace",
-                                            (torch.uint8,)),
+                                            _U8),
         workspace.numel(), _stream())
     _check(code, "wedlm_model_forward")
 
@@ -615,12 +625,12 @@ def wedlm_commit_layers(win_tok, win_start, argmax, entropy, tau: float,
     L, _, _, Hkv, D = k_win.shape
     P = k_cache.shape[1]
     maxp = block_table.shape[1]
-    i32 = (torch.int32,)
+    i32 = _I32
     code = _load().wedlm_commit_layers(
         _t(win_tok, "win_tok", i32, (B, W)),
         _t(win_start, "win_start", i32, (B,)),
         _t(argmax, "argmax", i32, (B, W)),
-        _t(entropy, "entropy", (torch.float32,), (B, W)), float(tau),
+        _t(entropy, "entropy", _F32, (B, W)), float(tau),
         float(lam), _t(k_win, "k_win", _BF16, (L, B, W, Hkv, D)),
         _t(v_win, "v_win", _BF16, (L, B, W, Hkv, D)),
         _t(k_cache, "k_cache", _BF16, (L, P, Hkv, PAGE_SIZE, D)),
@@ -629,7 +639,7 @@ def wedlm_commit_layers(win_tok, win_start, argmax, entropy, tau: float,
         _t(n_commit, "n_commit", i32, (B,)),
         _t(committed_tok, "committed_tok", i32, (B, W)),
         _t(committed_slot, "committed_slot", i32, (B, W)),
-        _t(selected, "selected", (torch.uint8,), (B, W)),
+        _t(selected, "selected", _U8, (B, W)),
         _t(status, "status", i32, (B,)), int(rule), _stream())
     _check(code, "wedlm_commit_layers")
 
@@ -740,7 +750,7 @@ def wedlm_dual_stream_attn(q, k, v, block: int, out, lse=None, workspace=None,
         _t(k, "k", _BF16, (n_seq, 2 * L, Hkv, D)),
         _t(v, "v", _BF16, (n_seq, 2 * L, Hkv, D)), n_seq, L, int(block), Hq,
         Hkv, D, float(softmax_scale), _t(out, "out", _BF16, (n_seq, 2 * L, Hq, D)),
-        _t(lse, "lse", (torch.float32,), (n_seq, 2 * L, Hq), allow_none=True),
-        _t(workspace, "workspace", (torch.uint8,)), workspace.numel(),
+        _t(lse, "lse", _F32, (n_seq, 2 * L, Hq), allow_none=True),
+        _t(workspace, "workspace", _U8), workspace.numel(),
         _stream())
     _check(code, "wedlm_dual_stream_attn")
