@@ -37,6 +37,7 @@
 #include "common.h"
 #include "internal.h"
 
+#include <algorithm>
 #include <mutex>
 
 using namespace wedlm;
@@ -81,6 +82,10 @@ struct AttnArgs {
   // Workgroups take the sequences from the last one down (callers whose
   // later sequences have the longer prefixes: the longest start first)
   int rev;
+  // by_len > 0: workgroups take the sequences by their prefix length, the
+  // by_len longest first (they land one per CU), then the others so that the
+  // shortest share a CU with the longest (see sequence_by_length)
+  int by_len;
   float scale_log2;       // softmax_scale * log2(e)
 };
 
@@ -182,6 +187,27 @@ __device__ __forceinline__ bool seq_ok(const AttnArgs& a, int b, int& c) {
          static_cast<int64_t>(c) <= static_cast<int64_t>(a.max_pages) * kPage;
 }
 
+// The sequence that slot (0 <= slot < B <= 64) takes when the workgroups go
+// by prefix length: slots 0 .. by_len-1 the longest, in falling order, then
+// the shortest in rising order if everything is resident at once (slot k and
+// slot by_len + k share a CU), else on in falling order.  One lane per
+// sequence; equal lengths keep their order, so every sequence has one slot.
+__device__ __forceinline__ int sequence_by_length(const AttnArgs& a, int slot) {
+  const int lane = lane_id();
+  const int len = a.plen[min(lane, a.B - 1)];
+  if (ballot(len != __builtin_amdgcn_readfirstlane(len)) == 0) return slot;
+  int rank = 0;
+#pragma unroll 4
+  for (int j = 0; j < a.B; ++j) {
+    const int l = __builtin_amdgcn_readlane(len, j);
+    rank += l > len || (l == len && j < lane) ? 1 : 0;
+  }
+  const int want = slot < a.by_len || a.B > 2 * a.by_len
+                       ? slot : a.B - 1 - (slot - a.by_len);
+  return __ffsll(static_cast<unsigned long long>(
+             ballot(lane < a.B && rank == want))) - 1;
+}
+
 typedef __attribute__((address_space(1))) void gbl_void_t;
 typedef __attribute__((address_space(4))) const int32_t const_i32_t;
 
@@ -270,7 +296,9 @@ void window_attn_kernel(AttnArgs a) {
   const int qb = wg % a.qblocks;
   wg /= a.qblocks;
   const int kvh = wg % a.Hkv;
-  const int b = a.rev ? a.B - 1 - wg / a.Hkv : wg / a.Hkv;
+  int b = a.rev ? a.B - 1 - wg / a.Hkv : wg / a.Hkv;
+  if (TWO && a.by_len > 0)
+    b = __builtin_amdgcn_readfirstlane(sequence_by_length(a, b));
 
   const int wave = threadIdx.x / kWave;
   const int lane = lane_id();
@@ -1071,6 +1099,15 @@ int window_attn_impl(
   a.max_pages = max_pages; a.max_prefix = max_prefix_len;
   a.nsplit = p.nsplit; a.qblocks = p.qblocks;
   a.rows_pad = p.rows_pad;
+  // Two workgroups per CU, all resident at once: a CU's time is that of the
+  // two prefixes it holds, so they are paired by length, for up to one
+  // sequence per lane.  Shuffled prefixes, 32/8 heads, W = 32, against taking
+  // the sequences in order: 64 of 512 to 4096 145 -> 124 us, 48 of 100 to
+  // 5000 146 -> 127, 32 of 512 to 4096 (two splits) 90 -> 82; equal ones keep
+  // their order (64 of 2304 113.8 -> 113.8).  The ordering itself takes about
+  // 0.6 us, so prefixes of less than 1024 (a call of 25 us) go without.
+  if (p.two && pair_half == 0 && B > 1 && B <= kWave && max_prefix_len >= 1024)
+    a.by_len = std::max(1, 256 / (Hkv * p.qblocks * p.nsplit));
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
   if (p.nsplit > 1) {
     const size_t n = static_cast<size_t>(B) * Hkv * p.rows_pad * p.nsplit;

@@ -476,3 +476,53 @@ def test_attention_status_bits():
     err = np.abs(out[b] - ref)
     assert err.max() <= PL.ATTN_MAX_ABS
     assert np.linalg.norm(out[b] - ref) / np.linalg.norm(ref) <= PL.ATTN_REL_NORM
+
+
+# sequences taken by prefix length (two workgroups per CU): equal lengths,
+# empty prefixes, one that is out of range, all equal, a batch of more than
+# two rounds of CUs, and splits
+@pytest.mark.parametrize("lens", [
+    [0, 0, 5, 333, 333, 40, 16, 1040] * 4, [1024] * 32,
+    [-1] + [1100 - 33 * i for i in range(31)],
+    [31 * (i % 7) for i in range(63)] + [1025],
+    [2048 + 64 * (i % 3) for i in range(16)]])
+def test_sequences_by_length(lens):
+    import torch
+    from paper_2512_22737_amd import wedlm
+    B, W, Hq, Hkv, D = len(lens), 48, 32, 16, 64
+    G, mp = Hq // Hkv, max(lens)
+    g = torch.Generator().manual_seed(B + mp)
+    bf = lambda *s: torch.randn(*s, generator=g).bfloat16()
+    npg = [-(-max(n, 1) // 16) for n in lens]
+    bt = torch.full((B, max(npg)), -1, dtype=torch.int32)
+    ids = torch.randperm(sum(npg), generator=g).to(torch.int32)
+    at = 0
+    for b, n in enumerate(npg):
+        bt[b, :n] = ids[at:at + n]
+        at += n
+    kc, vc = bf(at, Hkv, 16, D), bf(at, Hkv, D, 16)
+    q, k, v = bf(B, W, Hq, D), bf(B, W, Hkv, D), bf(B, W, Hkv, D)
+    n = wedlm.wedlm_window_attn_workspace_size(B, W, Hq, Hkv, D, mp)
+    assert (n > 0) == (B == 16)                 # the last case splits
+    out = torch.zeros(B, W, Hq, D, dtype=torch.bfloat16, device="cuda")
+    st = torch.zeros(B, dtype=torch.int32, device="cuda")
+    wedlm.wedlm_window_attn(
+        q.cuda(), k.cuda(), v.cuda(), kc.cuda(), vc.cuda(), bt.cuda(),
+        torch.tensor(lens, dtype=torch.int32, device="cuda"), mp, out, None,
+        st, torch.empty(max(n, 1), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert st.cpu().tolist() == [wedlm.SEQ_BAD_LEN if x < 0 else 0 for x in lens]
+    see = torch.ones(W, W).tril().bool()
+    for b, c in enumerate(lens):
+        if c < 0:
+            continue
+        pg = bt[b, :npg[b]].long()
+        kp = kc[pg].permute(0, 2, 1, 3).reshape(-1, Hkv, D)[:c]
+        vp = vc[pg].permute(0, 3, 1, 2).reshape(-1, Hkv, D)[:c]
+        ks, vs = torch.cat((kp, k[b])).float(), torch.cat((vp, v[b])).float()
+        m = torch.cat((torch.ones(W, c).bool(), see), 1)
+        for h in range(0, Hq, 5):
+            s = (q[b, :, h].float() @ ks[:, h // G].T * D ** -0.5)
+            r = torch.softmax(s.masked_fill(~m, float("-inf")), 1) @ vs[:, h // G]
+            d = (out[b, :, h].cpu().float() - r).abs().max()
+            assert d < PL.ATTN_MAX_ABS, (b, h, d)
