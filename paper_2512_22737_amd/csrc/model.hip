@@ -207,44 +207,55 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(
 // PART: the q|k|v row comes as the n_ks fp32 partials of a split product
 // ([n_ks, M, H*D]); they are added in split order and rounded to bf16 (the
 // product's own output precision) on the way in.
+// Bound by latency: 512 threads, so that a row of Qwen3-8B (320 items and 128
+// pieces of v) is one round, and an item's loads all go out together.  Two
+// partials of 512 rows (31 MB moved) 11.6 -> 9.7 us, 32 rows 5.4 -> 5.0,
+// against 256 threads whose first four waves did two rounds and the two
+// halves of an item one after the other (512 threads alone: 12.8).
 // ---------------------------------------------------------------------------
-constexpr int kQkThreads = 256;
+constexpr int kQkThreads = 512;
 constexpr int kMaxHalf = 64;
 
-template <bool PART>
-__device__ __forceinline__ u16x8_t qkv_load8(const uint16_t* x,
-                                             const float* part, int64_t pstride,
-                                             int n_ks, int64_t off) {
+// C pieces of 8 values of a row, at o[0] .. o[C-1].  PART: the first two
+// partials (n_ks >= 2) of all pieces are loaded before the first add, the
+// others two at a time; they are added in split order
+template <bool PART, int C>
+__device__ __forceinline__ void qkv_load8(const uint16_t* x, const float* part,
+                                          int64_t pstride, int n_ks,
+                                          const int64_t (&o)[C],
+                                          u16x8_t* const (&out)[C]) {
   if constexpr (!PART) {
-    return *reinterpret_cast<const u16x8_t*>(x + off);
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      *out[c] = *reinterpret_cast<const u16x8_t*>(x + o[c]);
   } else {
-    // partials loaded four at a time, added in split order
-    floatx4_t lo = *reinterpret_cast<const floatx4_t*>(part + off);
-    floatx4_t hi = *reinterpret_cast<const floatx4_t*>(part + off + 4);
-    for (int k0 = 1; k0 < n_ks; k0 += 4) {
-      floatx4_t a[4], b[4];
+    floatx4_t s[2 * C], a[2 * C], b[2 * C];
+    auto load = [&](floatx4_t* d, int k) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = k0 + u < n_ks ? k0 + u : n_ks - 1;
-        a[u] = *reinterpret_cast<const floatx4_t*>(part + k * pstride + off);
-        b[u] = *reinterpret_cast<const floatx4_t*>(part + k * pstride + off + 4);
-      }
+      for (int c = 0; c < 2 * C; ++c)
+        d[c] = *reinterpret_cast<const floatx4_t*>(part + k * pstride +
+                                                   o[c / 2] + 4 * (c % 2));
+    };
+    auto add = [&](const floatx4_t* d) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (k0 + u < n_ks)
+      for (int c = 0; c < 2 * C; ++c)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            lo[e] += a[u][e];
-            hi[e] += b[u][e];
-          }
+        for (int e = 0; e < 4; ++e) s[c][e] += d[c][e];
+    };
+    load(s, 0);
+    load(a, 1);
+    add(a);
+    for (int k = 2; k < n_ks; k += 2) {
+      load(a, k);
+      load(b, min(k + 1, n_ks - 1));
+      add(a);
+      if (k + 1 < n_ks) add(b);
     }
-    u16x8_t r;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      r[e] = f32_to_bf16(lo[e]);
-      r[e + 4] = f32_to_bf16(hi[e]);
-    }
-    return r;
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        (*out[c])[e] = f32_to_bf16(s[2 * c + e / 4][e % 4]);
   }
 }
 
@@ -264,23 +275,22 @@ __global__ __launch_bounds__(kQkThreads) void qk_norm_rope_kernel(
   const int64_t row = static_cast<int64_t>(t) * H * D;   // element offset
   const int64_t pstride = static_cast<int64_t>(M) * H * D;
   const int nv = Hkv * D / 8;                     // 16-byte pieces of v
-  // the first two rounds of q/k items and the first round of v are loaded
-  // before the rotation table is computed, so its fp64 trigonometry runs
-  // under their round trip
+  // the pieces of v follow the q/k items, one thread each.  The first round
+  // is loaded before the rotation table is computed, so its fp64
+  // trigonometry runs under that round trip
   auto load_item = [&](int it, u16x8_t& lo8, u16x8_t& hi8) {
     if (it < n_items) {
       const int head = it / per_head;
       const int j0 = (it - head * per_head) * 8;
-      lo8 = qkv_load8<PART>(qkv, part, pstride, n_ks, row + head * D + j0);
-      hi8 = qkv_load8<PART>(qkv, part, pstride, n_ks, row + head * D + j0 + half);
+      const int64_t o = row + head * D + j0;
+      qkv_load8<PART, 2>(qkv, part, pstride, n_ks, {o, o + half}, {&lo8, &hi8});
+    } else if (it < n_items + nv) {
+      qkv_load8<PART, 1>(qkv, part, pstride, n_ks,
+                         {row + (Hq + Hkv) * D + (it - n_items) * 8}, {&lo8});
     }
   };
-  u16x8_t lo0 = {}, hi0 = {}, lo1 = {}, hi1 = {}, v0 = {};
+  u16x8_t lo0 = {}, hi0 = {};
   load_item(threadIdx.x, lo0, hi0);
-  load_item(threadIdx.x + kQkThreads, lo1, hi1);
-  if (threadIdx.x < nv)
-    v0 = qkv_load8<PART>(qkv, part, pstride, n_ks,
-                         row + (Hq + Hkv) * D + threadIdx.x * 8);
 
   __shared__ double s_cos[kMaxHalf], s_sin[kMaxHalf];
   if (threadIdx.x < half) {
@@ -295,6 +305,8 @@ __global__ __launch_bounds__(kQkThreads) void qk_norm_rope_kernel(
   __syncthreads();
   // n_items is a multiple of per_head and every round starts at a multiple
   // of kQkThreads, so a head's items never straddle a round or a wave
+  u16x8_t* dv =
+      reinterpret_cast<u16x8_t*>(v_out + static_cast<int64_t>(t) * Hkv * D);
   auto rotate = [&](int it, const u16x8_t& lo8, const u16x8_t& hi8) {
     const bool live = it < n_items;
     const int head = live ? it / per_head : 0;
@@ -307,7 +319,10 @@ __global__ __launch_bounds__(kQkThreads) void qk_norm_rope_kernel(
       ss += a[e] * a[e] + b[e] * b[e];
     }
     for (int off = 1; off < per_head; off <<= 1) ss += __shfl_xor(ss, off);
-    if (!live) return;
+    if (!live) {
+      if (it < n_items + nv) dv[it - n_items] = lo8;
+      return;
+    }
     const float r = 1.0f / sqrtf(ss / static_cast<float>(D) + eps);
     const uint16_t* g = head < Hq ? gq : gk;
     u16x8_t olo, ohi;
@@ -326,17 +341,11 @@ __global__ __launch_bounds__(kQkThreads) void qk_norm_rope_kernel(
     *reinterpret_cast<u16x8_t*>(dst + j0 + half) = ohi;
   };
   rotate(threadIdx.x, lo0, hi0);
-  if (n_items > kQkThreads) rotate(threadIdx.x + kQkThreads, lo1, hi1);
-  for (int base = 2 * kQkThreads; base < n_items; base += kQkThreads) {
+  for (int base = kQkThreads; base < n_items + nv; base += kQkThreads) {
     u16x8_t lo8 = {}, hi8 = {};
     load_item(base + threadIdx.x, lo8, hi8);
     rotate(base + threadIdx.x, lo8, hi8);
   }
-  u16x8_t* dv =
-      reinterpret_cast<u16x8_t*>(v_out + static_cast<int64_t>(t) * Hkv * D);
-  if (threadIdx.x < nv) dv[threadIdx.x] = v0;
-  for (int e = threadIdx.x + kQkThreads; e < nv; e += kQkThreads)
-    dv[e] = qkv_load8<PART>(qkv, part, pstride, n_ks, row + (Hq + Hkv) * D + e * 8);
 }
 
 // ---------------------------------------------------------------------------

@@ -128,6 +128,14 @@ def test_qk_norm_rope(M, Hq, Hkv, D):
                           qkv.reshape(M, Hq + 2 * Hkv, D)[:, Hq + Hkv:])
 
 
+# rounds of 512 threads: v after the items within one round, from the second
+# round on, across its edge, and with fewer pieces than a wave
+@pytest.mark.parametrize("M,Hq,Hkv,D", [(3, 12, 12, 64), (2, 48, 16, 128),
+                                        (3, 50, 10, 128), (2, 1, 1, 64)])
+def test_qk_norm_rope_rounds(M, Hq, Hkv, D):
+    test_qk_norm_rope(M, Hq, Hkv, D)
+
+
 def test_pack_layout_exact():
     """The packed tile layout of include/wedlm_model.h, element by element."""
     w = W_()
