@@ -698,8 +698,318 @@ void add_partials(float* x, int ldx, const float* part, int n_ks, int M, int N,
 }
 
 // ---------------------------------------------------------------------------
-// 2-D tiled GEMM for many window rows.  A workgroup of eight waves computes
-// FG feature groups x 128 tokens (4 row tiles) over its run of K steps; a
+// 2-D tiled GEMM of the decoder's packed activations (k2pMinRows rows and
+// more: batches of windows).  A workgroup computes 256 features (8 blocks; for SwiGLU 4 gate blocks and
+// their 4 up blocks) x 128 tokens (4 row tiles) over its run of K steps.
+// Per 64-wide step the 12 packed 4 KB tiles (8 weight, 4 activation) go
+// from HBM into LDS as they are, with LDS-destination buffer loads (the
+// packed layout is already the MFMA operand order, so every fragment read
+// is 16 contiguous bytes per lane and no register holds a tile in
+// transit); each of the 8 waves computes a 64 x 64 piece (2 feature blocks
+// x 2 row tiles, 16 MFMAs per step), so every LDS byte a wave reads feeds
+// two MFMAs.  A ring of three LDS stages: the tiles of step s+2 load while
+// step s computes, one barrier per step.  A decoder step keeps these 32x32x16
+// MFMAs and their order of sums: in the 16x16x32 form of the row-major
+// kernel below a layer of 512 rows takes 5% less, but the bf16 roundings
+// that move with the sums travel through the layers, and greedy tokens whose
+// two best logits are within about 0.01 came out otherwise.
+// ---------------------------------------------------------------------------
+constexpr int k2pFeat = 8;                        // feature blocks per WG
+constexpr int k2pTok = 4;                         // row tiles per WG
+constexpr int k2pTiles = k2pFeat + k2pTok;        // 12 tiles per step
+constexpr int k2pStage = k2pTiles * kTile * 2;    // 48 KB per LDS buffer
+constexpr int k2pChunks = k2pTiles * 4 / kGWaves;       // 1 KB chunks per wave: 6
+constexpr int k2pStages = 3;                      // LDS ring: 144 KB
+
+struct Gemm2dArgs {
+  const uint16_t* x;      // activations, packed row tiles or row-major
+  const uint16_t* w;      // packed weights
+  void* out;
+  float* part;            // n_ks > 1 (residual add, stored q|k|v): [n_ks, M, N]
+  int M, N, K, ldo;
+  int n_fb;               // 32-feature blocks of the output (N / 32)
+  int n_ft, n_tt, n_ks;   // feature tiles, row tiles, K splits
+};
+
+template <int EPI>
+__global__ __launch_bounds__(kGThreads) void gemm2d_packed_kernel(Gemm2dArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds2[k2pStages * k2pStage];
+  // tile order: the K splits and row tiles of one feature tile on one XCD
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+  const int per_ft = a.n_tt * a.n_ks;
+  const int ft = xcd + 8 * (local / per_ft);
+  const int tt = (local % per_ft) / a.n_ks;
+  const int ks = local % a.n_ks;
+  if (ft >= a.n_ft) return;                          // whole workgroup
+
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int S = a.K / kKStep;
+  const int s0 = ks * S / a.n_ks, s1 = (ks + 1) * S / a.n_ks;
+  const int n = s1 - s0;                             // >= 1 (plan)
+  const int last_rt = (a.M - 1) / 32;
+
+  // weight block of LDS tile i (0..7): consecutive feature blocks, or for
+  // SwiGLU gate blocks 0..3 then their up blocks (clamped at the end: those
+  // outputs are never stored)
+  const int out_blocks = EPI == kSwiglu ? k2pFeat / 2 : k2pFeat;
+  auto wblock = [&](int i) {
+    const int f = ft * out_blocks + (EPI == kSwiglu ? (i & 3) : i);
+    const int fc = min(f, a.n_fb - 1);
+    return (EPI == kSwiglu && i >= 4) ? fc + a.n_fb : fc;
+  };
+  // The 48 KB of a step go straight from HBM into its LDS stage: wave w
+  // moves the 1 KB chunks c = 6w .. 6w+5 (tile c / 4, MFMA j = c % 4), one
+  // load instruction each, lane l's 16 bytes landing at byte 16 l of the
+  // chunk, which is where the packed layout already keeps them.  Each chunk
+  // is read through a buffer resource over its tile's run of steps.
+  const uint32_t lds0 =
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds2));
+  i32x4_t rs[k2pChunks];
+#pragma unroll
+  for (int u = 0; u < k2pChunks; ++u) {
+    const int tile = (wave * k2pChunks + u) >> 2;
+    const int64_t blk = tile < k2pFeat ? wblock(tile)
+                                       : min(tt * k2pTok + tile - k2pFeat, last_rt);
+    rs[u] = buffer_rsrc((tile < k2pFeat ? a.w : a.x) + (blk * S + s0) * kTile,
+                        n * kTile * 2);
+  }
+  auto issue = [&](int q, int stage) {
+    const int qq = min(q, n - 1);                    // past the run: re-read
+#pragma unroll
+    for (int u = 0; u < k2pChunks; ++u) {
+      const int c = wave * k2pChunks + u;
+      load_to_lds16<false>(
+          rs[u], qq * kTile * 2 + (c & 3) * 1024 + lane * 16,
+          __builtin_amdgcn_readfirstlane(lds0 + stage * k2pStage + c * 1024));
+    }
+  };
+  // wave tile: feature blocks fb0, fb0+1 (SwiGLU: gate fw and up fw + 4) x
+  // row tiles 2*tw, 2*tw+1 of the workgroup
+  const int fw = wave & 3, tw = wave >> 2;
+  const int fa = EPI == kSwiglu ? fw : 2 * fw;
+  const int fb = EPI == kSwiglu ? fw + 4 : 2 * fw + 1;
+  floatx16_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  auto compute = [&](int buf) {
+    const char* base = lds2 + buf * k2pStage + lane * 16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t*>(base + fa * 4096 + j * 1024);
+      const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(base + fb * 4096 + j * 1024);
+      const bf16x8_t b0 = *reinterpret_cast<const bf16x8_t*>(
+          base + (k2pFeat + 2 * tw) * 4096 + j * 1024);
+      const bf16x8_t b1 = *reinterpret_cast<const bf16x8_t*>(
+          base + (k2pFeat + 2 * tw + 1) * 4096 + j * 1024);
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
+      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[0][1], 0, 0, 0);
+      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1][0], 0, 0, 0);
+      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1][1], 0, 0, 0);
+    }
+  };
+
+  // step q computes from stage q % 3 while the loads of step q+2 fill stage
+  // (q+2) % 3, read last in step q-1 (before the barrier that ended it);
+  // before the barrier that ends step q every wave waits for its loads of
+  // step q+1, leaving only those of q+2 in flight.
+  issue(0, 0);
+  issue(1, 1);
+  wait_vmcnt<k2pChunks>();
+  __syncthreads();
+  for (int q = 0; q < n; ++q) {
+    issue(q + 2, (q + 2) % k2pStages);
+    compute(q % k2pStages);
+    wait_vmcnt<k2pChunks>();
+    __syncthreads();
+  }
+  wait_vmcnt<0>();   // surplus re-reads retire before the workgroup ends
+
+  // epilogue from registers: lane l, element e = 4g + r is feature
+  // 8g + 4(l/32) + r of its block and token l%32 of its row tile, so the 4
+  // values of a group are 4 consecutive features of one token
+  const int hf = lane >> 5, col = lane & 31;
+#pragma unroll
+  for (int tj = 0; tj < 2; ++tj) {
+    const int tok = (tt * k2pTok + 2 * tw + tj) * 32 + col;
+    if (tok >= a.M) continue;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if constexpr (EPI == kSwiglu) {
+        const int f = (ft * (k2pFeat / 2) + fw) * 32 + 8 * g + 4 * hf;
+        if (f >= a.N) continue;
+        u16x4_t o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float gg = acc[0][tj][4 * g + r], uu = acc[1][tj][4 * g + r];
+          o[r] = f32_to_bf16(gg / (1.0f + expf(-gg)) * uu);
+        }
+        *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) +
+                                    packed_off(tok, f, a.N)) = o;
+      } else {
+#pragma unroll
+        for (int fi = 0; fi < 2; ++fi) {
+          const int f = (ft * k2pFeat + (fi ? fb : fa)) * 32 + 8 * g + 4 * hf;
+          if (f >= a.N) continue;
+          floatx4_t v;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = acc[fi][tj][4 * g + r];
+          const int64_t o = static_cast<int64_t>(tok) * a.ldo + f;
+          if (EPI == kStoreBf16 && a.n_ks == 1) {
+            u16x4_t h;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h[r] = f32_to_bf16(v[r]);
+            *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) + o) = h;
+          } else if (EPI == kAddF32 && a.n_ks == 1) {
+            floatx4_t* p = reinterpret_cast<floatx4_t*>(static_cast<float*>(a.out) + o);
+            const floatx4_t old = *p;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] += old[r];
+            *p = v;
+          } else {
+            *reinterpret_cast<floatx4_t*>(
+                a.part + (static_cast<int64_t>(ks) * a.M + tok) * a.N + f) = v;
+          }
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Wide SwiGLU tiles for large grids: a workgroup computes 128 features
+// (gate blocks 0..3 and their up blocks) x 256 tokens (8 row tiles) over
+// the whole K.  Wave w takes gate block w%4 and its up block x row tiles
+// 4(w/4) .. 4(w/4)+3: each A fragment read from LDS feeds four MFMAs and
+// each B fragment two, 0.75 KB of LDS reads per MFMA against 1 KB in the
+// kernel above.  Per step the 16 packed tiles (64 KB) go to LDS as there;
+// a ring of two stages (128 KB): the tiles of step s+1 load while step s
+// computes.  Each output element sums its k steps in the same order as the
+// kernel above, so the two give the same bits.  Used when its grid fills
+// most of the chip (at 512 rows and 12288 features: 92-99 against 109-127
+// us); on smaller grids the 128-token tiles are faster.
+// ---------------------------------------------------------------------------
+constexpr int kWTok = 8;                          // row tiles per WG
+constexpr int kWTiles = k2pFeat + kWTok;          // 16 tiles per step
+constexpr int kWStage = kWTiles * kTile * 2;      // 64 KB per LDS buffer
+constexpr int kWChunks = kWTiles * 4 / kGWaves;   // 1 KB chunks per wave: 8
+constexpr int kWStages = 2;                       // LDS ring: 128 KB
+
+__global__ __launch_bounds__(kGThreads) void gemm2d_packed_wide_kernel(
+    Gemm2dArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds2[kWStages * kWStage];
+  // tile order: the row tiles of one feature tile on one XCD
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+  const int ft = xcd + 8 * (local / a.n_tt);
+  const int tt = local % a.n_tt;
+  if (ft >= a.n_ft) return;                          // whole workgroup
+
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = a.K / kKStep;
+  const int last_rt = (a.M - 1) / 32;
+  // gate blocks 0..3 then their up blocks (clamped at the end: those
+  // outputs are never stored)
+  auto wblock = [&](int i) {
+    const int f = ft * (k2pFeat / 2) + (i & 3);
+    const int fc = min(f, a.n_fb - 1);
+    return i >= 4 ? fc + a.n_fb : fc;
+  };
+  // wave w moves the 1 KB chunks c = 8w .. 8w+7 (tile c / 4, MFMA c % 4)
+  const uint32_t lds0 =
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds2));
+  i32x4_t rs[kWChunks];
+#pragma unroll
+  for (int u = 0; u < kWChunks; ++u) {
+    const int tile = (wave * kWChunks + u) >> 2;
+    const int64_t blk = tile < k2pFeat
+                            ? wblock(tile)
+                            : min(tt * kWTok + tile - k2pFeat, last_rt);
+    rs[u] = buffer_rsrc((tile < k2pFeat ? a.w : a.x) + blk * n * kTile,
+                        n * kTile * 2);
+  }
+  auto issue = [&](int q, int stage) {
+    const int qq = min(q, n - 1);                    // past the run: re-read
+#pragma unroll
+    for (int u = 0; u < kWChunks; ++u) {
+      const int c = wave * kWChunks + u;
+      load_to_lds16<false>(
+          rs[u], qq * kTile * 2 + (c & 3) * 1024 + lane * 16,
+          __builtin_amdgcn_readfirstlane(lds0 + stage * kWStage + c * 1024));
+    }
+  };
+  const int fw = wave & 3, tw = wave >> 2;
+  floatx16_t acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  auto compute = [&](int buf) {
+    const char* base = lds2 + buf * kWStage + lane * 16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bf16x8_t a0 =
+          *reinterpret_cast<const bf16x8_t*>(base + fw * 4096 + j * 1024);
+      const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(
+          base + (fw + 4) * 4096 + j * 1024);
+      bf16x8_t b[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        b[t] = *reinterpret_cast<const bf16x8_t*>(
+            base + (k2pFeat + 4 * tw + t) * 4096 + j * 1024);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[t], acc[0][t], 0, 0, 0);
+        acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[t], acc[1][t], 0, 0, 0);
+      }
+    }
+  };
+
+  // step q computes from stage q % 2 while the loads of step q+1 fill the
+  // other stage, read last in step q-1 (before the barrier that ended it);
+  // before the barrier that ends step q every wave waits for its loads.
+  issue(0, 0);
+  wait_vmcnt<0>();
+  __syncthreads();
+  for (int q = 0; q < n; ++q) {
+    issue(q + 1, (q + 1) & 1);
+    compute(q & 1);
+    wait_vmcnt<0>();
+    __syncthreads();
+  }
+
+  // epilogue as in gemm2d_packed_kernel (lane l, element 4g + r: feature
+  // 8g + 4(l/32) + r of its block, token l%32 of its row tile)
+  const int hf = lane >> 5, col = lane & 31;
+#pragma unroll
+  for (int tj = 0; tj < 4; ++tj) {
+    const int tok = (tt * kWTok + 4 * tw + tj) * 32 + col;
+    if (tok >= a.M) continue;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int f = (ft * (k2pFeat / 2) + fw) * 32 + 8 * g + 4 * hf;
+      if (f >= a.N) continue;
+      u16x4_t o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float gg = acc[0][tj][4 * g + r], uu = acc[1][tj][4 * g + r];
+        o[r] = f32_to_bf16(gg / (1.0f + expf(-gg)) * uu);
+      }
+      *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) +
+                                  packed_off(tok, f, a.N)) = o;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 2-D tiled GEMM for many rows of row-major activations (wedlm_linear).  A
+// workgroup of eight waves computes FG feature groups x 128 tokens (4 row tiles) over its run of K steps; a
 // feature group is two 32-feature blocks (for SwiGLU a gate block and its up
 // block) and belongs to one wave (WK = 1: eight groups, 512 features) or to
 // two (WK = 2: four groups, 256 features), which then take alternate k steps
@@ -715,34 +1025,22 @@ void add_partials(float* x, int ldx, const float* part, int n_ks, int M, int N,
 //   activations  (shared by the waves) go into an LDS ring of four stages
 //                (one k step per wave of a group, 16 KB each) with
 //                LDS-destination buffer loads, three stages ahead, one
-//                barrier per stage.  Packed tiles are copied as they are;
-//                row-major rows (XP false) land as 128-byte rows of XOR-
+//                barrier per stage.  They land as 128-byte rows of XOR-
 //                swizzled 16-byte chunks (each lane fetches the chunk that
 //                belongs at its place).  A stage is published one barrier
 //                before its own, so fragments are read four ahead across the
 //                barrier and the MFMAs never wait for it to refill them.
 // A wave's 64 x 128 piece takes 32 MFMAs per 8 LDS reads of 1 KB.
-// Measured (in a decoder layer of 512 packed rows): gate/up 111 -> 103 us
-// (1.0 PFLOP/s), down and o together 115 -> 100 us, against 64 x 64 wave
-// pieces with both operands in LDS; row-major (no such path before), down at
-// 512 rows 240 -> 63 us with its sum.  With every load left out of the loop
-// gate/up takes 77 us, with weights that stay in L2 92: what is left is the
-// latency of the weight stream at two stages ahead.
+// Measured against the split-K kernel (the only row-major path before): down
+// (4096 x 12288) at 512 rows 240 -> 63 us with its sum, gate/up (12288 x
+// 4096) 333 -> 99.  With every load left out of the loop gate/up takes 77 us,
+// with weights that stay in L2 92: what is left is the weight stream, whose
+// waits the compiler places without counting the LDS-destination loads.
 // ---------------------------------------------------------------------------
 constexpr int k2dTok = 4;                         // row tiles per WG
 constexpr int k2dSub = k2dTok * kTile * 2;        // one k step in LDS: 16 KB
 constexpr int k2dRing = 4;                        // LDS stages
 constexpr int k2dLead = 3;                        // stages loaded ahead
-
-struct Gemm2dArgs {
-  const uint16_t* x;      // activations, packed row tiles or row-major
-  const uint16_t* w;      // packed weights
-  void* out;
-  float* part;            // n_ks > 1 (residual add, stored q|k|v): [n_ks, M, N]
-  int M, N, K, ldo;
-  int n_fb;               // 32-feature blocks of the output (N / 32)
-  int n_ft, n_tt, n_ks;   // feature tiles, row tiles, K splits
-};
 
 // XOR swizzle of the 16-byte chunks of a row-major LDS row (128 bytes): the
 // lanes that one pass of ds_read_b128 serves together (0-3, 12-15, 20-23,
@@ -752,7 +1050,7 @@ __device__ __forceinline__ int x_swz(int r) {
   return ((r >> 1) & 1) | ((r >> 2) & 2);
 }
 
-template <int EPI, bool XP, int WK>
+template <int EPI, int WK>
 __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
   constexpr int FG = kGWaves / WK;                 // feature groups
   constexpr int kStage = WK * k2dSub;              // LDS bytes of a stage
@@ -761,6 +1059,7 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
   constexpr int kT = 2 * k2dTok;                   // 16-token columns
   constexpr int kFr = 2 * kT;                      // fragments per stage
   constexpr int kAhead = 4;                        // read ahead of their use
+  constexpr int kStepBytes = kKStep * 2;           // of a row, per k step
   static_assert(k2dRing >= k2dLead + 1 && k2dLead >= 2, "slot reuse");
   static_assert(WK == 1 || k2dRing * kStage >= kGWaves * 16384, "exchange");
   __shared__ __attribute__((aligned(1024))) char lds2[k2dRing * kStage];
@@ -803,38 +1102,25 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
   };
 
   // ---- activations: 1 KB chunk c = wave*kDma + u of a stage is k step
-  // c / 16 of the stage; packed, MFMA c % 4 of row tile c / 4 % 4; row-major,
-  // the 128-byte rows 8 (c % 16) .. + 7.  Rows past M read its last row (or
-  // tile): their outputs are never stored, but every load reads memory, since
-  // one wholly out of a resource's range is counted done ahead of older ones.
+  // c / 16 of the stage, the 128-byte rows 8 (c % 16) .. + 7.  Rows past M
+  // read its last row: their outputs are never stored, but every load reads
+  // memory, since one wholly out of a resource's range is counted done ahead
+  // of older ones.
   const uint32_t lds0 =
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds2));
   int d_off[kDma], d_sub[kDma];
-  i32x4_t rs;
-  if constexpr (XP) {
-    const int last = min((a.M - 1) / 32 - tt * k2dTok, k2dTok - 1);
-    rs = buffer_rsrc(a.x + (static_cast<int64_t>(tt) * k2dTok * S + s0) * kTile,
-                     (last * S + n) * kTile * 2);
+  const int row0 = tt * k2dTok * 32;
+  const int last = min(a.M - row0, k2dTok * 32) - 1;
+  const i32x4_t rs =
+      buffer_rsrc(a.x + static_cast<int64_t>(row0) * a.K + s0 * kKStep,
+                  last * a.K * 2 + n * kStepBytes);
 #pragma unroll
-    for (int u = 0; u < kDma; ++u) {
-      const int c = wave * kDma + u;
-      d_sub[u] = c / 16;
-      d_off[u] = min(c / 4 % 4, last) * S * kTile * 2 + (c & 3) * 1024 + lane * 16;
-    }
-  } else {
-    const int row0 = tt * k2dTok * 32;
-    const int last = min(a.M - row0, k2dTok * 32) - 1;
-    rs = buffer_rsrc(a.x + static_cast<int64_t>(row0) * a.K + s0 * kKStep,
-                     last * a.K * 2 + n * kKStep * 2);
-#pragma unroll
-    for (int u = 0; u < kDma; ++u) {
-      const int c = wave * kDma + u;
-      d_sub[u] = c / 16;
-      const int r = c % 16 * 8 + (lane >> 3);
-      d_off[u] = min(r, last) * a.K * 2 + (((lane & 7) ^ x_swz(r)) << 4);
-    }
+  for (int u = 0; u < kDma; ++u) {
+    const int c = wave * kDma + u;
+    d_sub[u] = c / 16;
+    const int r = c % 16 * 8 + (lane >> 3);
+    d_off[u] = min(r, last) * a.K * 2 + (((lane & 7) ^ x_swz(r)) << 4);
   }
-  constexpr int kStepBytes = XP ? kTile * 2 : kKStep * 2;
   auto dma = [&](int q, int slot) {
 #pragma unroll
     for (int u = 0; u < kDma; ++u) {
@@ -849,14 +1135,12 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
   const char* bl[2];
 #pragma unroll
   for (int sl = 0; sl < 2; ++sl)
-    bl[sl] = lds2 + kh * k2dSub +
-             (XP ? l_pack * 2 + sl * 2048
-                 : lr * 128 +
-                       (((4 * (lg & 1) + 2 * sl + (lg >> 1)) ^ x_swz(lr)) << 4));
+    bl[sl] = lds2 + kh * k2dSub + lr * 128 +
+             (((4 * (lg & 1) + 2 * sl + (lg >> 1)) ^ x_swz(lr)) << 4);
   auto bfrag = [&](int slot, int f) {
     const int t = f % kT;
     return *reinterpret_cast<const bf16x8_t*>(
-        bl[f / kT] + slot * kStage + t / 2 * 4096 + (t & 1) * (XP ? 256 : 2048));
+        bl[f / kT] + slot * kStage + t * 2048);
   };
 
   floatx4_t acc[4][kT];
@@ -935,10 +1219,8 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
           const float gg = c[h][r], uu = c[2 + h][r];
           o[r] = f32_to_bf16(gg / (1.0f + expf(-gg)) * uu);
         }
-        uint16_t* const op = static_cast<uint16_t*>(a.out);
-        *reinterpret_cast<u16x4_t*>(
-            XP ? op + packed_off(tok, f, a.N)
-               : op + static_cast<int64_t>(tok) * a.ldo + f) = o;
+        *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(a.out) +
+                                    static_cast<int64_t>(tok) * a.ldo + f) = o;
       } else {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -1103,8 +1385,9 @@ struct GemmPlan {
   int nw;                 // waves per workgroup of the split-K kernel
   int spw, wgs;           // spw > 0: its persistent form, steps per wave and
                           // workgroups
-  bool two_d;             // the 2-D tiled kernel
-  int wk;                 // its waves per feature group
+  bool two_d;             // a 2-D tiled kernel
+  bool wide;              // packed activations: its 256-token SwiGLU tiles
+  int wk;                 // row-major ones: its waves per feature group
   int n_ft, n_tt;         // its feature and row tiles
   size_t part_bytes;
 };
@@ -1112,8 +1395,16 @@ struct GemmPlan {
 // workgroups a split product aims at: about one per CU (with few rows, 512
 // and 768 made the 36-layer step at B = 1 slower: 5.00 -> 5.29 and 5.91 ms)
 constexpr int kGemmTargetWgs = 256;
+// window rows from which packed activations go through the 2-D kernel (at
+// 128 rows the split-K kernel is faster: 8.1 against 9.9 ms per 36-layer
+// step)
+constexpr int k2pMinRows = 256;
+// the wide SwiGLU tiles from this many workgroups (three quarters of the
+// CUs; at 96 or 128 workgroups the 128-token tiles measured faster)
+constexpr int kWideMinWgs = 3 * kGemmTargetWgs / 4;
+
 // The plan of the split-K kernel (few rows).
-GemmPlan rows_plan(int M, int N, int K, int epi, bool split_store) {
+GemmPlan rows_plan(int M, int N, int K, int epi, bool xp, bool split_store) {
   GemmPlan p{};
   p.nb = gemm_nb(M, epi == kSwiglu);
   p.n_nb = N / 32;
@@ -1133,10 +1424,12 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool split_store) {
     p.n_ks = std::max(1, std::min(kGemmTargetWgs / wgs, K / kKStep / kGWaves));
   }
   // the persistent form: the blocks in as few rounds as of one workgroup per
-  // CU, each workgroup taking the same number of them
+  // CU, each workgroup taking the same number of them.  Not for the decoder's
+  // residual adds (hidden above 8192), whose sums it would take in another
+  // order: eight waves, then one add, for two or four waves per split
   const int spw = K / kKStep / kGWaves;
   if (p.nb == 1 && p.n_nb > kGemmTargetWgs && K % (kKStep * kGWaves) == 0 &&
-      (spw == 8 || spw == 4)) {
+      (spw == 8 || spw == 4) && !(xp && epi == kAddF32)) {
     const int rounds = (p.n_nb + kGemmTargetWgs - 1) / kGemmTargetWgs;
     p.spw = spw;
     p.nw = kGWaves;
@@ -1151,46 +1444,67 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool split_store) {
 template <int SPW, bool XP>
 void persistent_launch(const GemmArgs& a, int epi, int wgs, hipStream_t st) {
   using Kernel = void (*)(GemmArgs);
-  const Kernel k =
-      epi == kSwiglu   ? gemm_persistent_kernel<2, SPW, kSwiglu, XP>
-      : epi == kAddF32 ? gemm_persistent_kernel<1, SPW, kAddF32, XP>
-                       : gemm_persistent_kernel<1, SPW, kStoreBf16, XP>;
+  Kernel k = epi == kSwiglu ? gemm_persistent_kernel<2, SPW, kSwiglu, XP>
+                            : gemm_persistent_kernel<1, SPW, kStoreBf16, XP>;
+  if constexpr (!XP)
+    if (epi == kAddF32) k = gemm_persistent_kernel<1, SPW, kAddF32, false>;
   hipLaunchKernelGGL(k, dim3(wgs), dim3(kGThreads), 0, st, a);
 }
 
-// Estimates of a product's time in microseconds, fitted to products of 33 to
-// 1024 rows, N 512 to 12288 and K 1024 to 12288.  Partials are written and
-// read at 4.5 to 6 TB/s; a launch that sums them takes 4 us, a norm that does
-// about 0.5 us per split.
-double partials_us(int n_ks, int M, int N, bool deferred) {
-  if (n_ks <= 1) return 0;
-  const double mb = 8e-6 * n_ks * M * N;
-  return deferred ? mb / 6 + 0.5 * n_ks : mb / 4.5 + 4;
+// Packed activations: 2-D tiles from k2pMinRows rows on.
+GemmPlan packed_plan(int M, int N, int K, int epi, bool split_store) {
+  if (M < k2pMinRows) return rows_plan(M, N, K, epi, true, split_store);
+  GemmPlan p{};
+  p.two_d = true;
+  p.n_nb = N / 32;
+  p.n_ft = (p.n_nb + (epi == kSwiglu ? 3 : 7)) / (epi == kSwiglu ? 4 : 8);
+  p.n_tt = (M + 32 * k2pTok - 1) / (32 * k2pTok);
+  p.n_ks = 1;
+  if (epi == kSwiglu) {
+    const int n_tt_w = (M + 32 * kWTok - 1) / (32 * kWTok);
+    if (p.n_ft * n_tt_w >= kWideMinWgs) {
+      p.wide = true;
+      p.n_tt = n_tt_w;
+    }
+  } else {
+    // a residual-add product with few tiles splits K (at least four steps per
+    // split); so does a stored one (q|k|v), whose fp32 partials are summed
+    // into bf16 right after
+    p.n_ks = std::max(1, std::min(kGemmTargetWgs / (p.n_ft * p.n_tt),
+                                  K / kKStep / 4));
+  }
+  if (p.n_ks > 1)
+    p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);
+  return p;
+}
+
+// Estimates of a product's time in microseconds, row-major activations,
+// fitted to products of 33 to 1024 rows, N 512 to 12288 and K 1024 to 12288.
+// Partials are written and read at 4.5 TB/s, the launch that sums them takes
+// 4 us.
+double partials_us(int n_ks, int M, int N) {
+  return n_ks <= 1 ? 0 : 8e-6 / 4.5 * n_ks * M * N + 4;
 }
 
 // The split-K kernel: a round of one workgroup per CU runs S / (8 n_ks) steps
-// of NA * NB MFMA groups per wave (row-major activations cost more: their
-// lanes read 64 bytes of 32 rows per load).
-double rows_us(const GemmPlan& p, int M, int N, int K, int epi, bool xp,
-               bool deferred) {
+// of NA * NB MFMA groups per wave (its lanes read 64 bytes of 32 rows of
+// activations per load).
+double rows_us(const GemmPlan& p, int M, int N, int K, int epi) {
   const double rounds =
       std::max(1.0, static_cast<double>(p.n_nb) * p.n_rg * p.n_ks / kGemmTargetWgs);
   const int steps = (K / kKStep + p.nw * p.n_ks - 1) / (p.nw * p.n_ks);
   const int groups = p.nb * (epi == kSwiglu ? 2 : 1);
-  return (xp ? 5 + rounds * steps * groups * 0.67
-             : 1.5 + rounds * steps * (1.6 + 0.9 * groups)) +
-         partials_us(p.n_ks, M, N, deferred);
+  return 1.5 + rounds * steps * (1.6 + 0.9 * groups) +
+         partials_us(p.n_ks, M, N);
 }
 
-// Products of more than 32 rows take the 2-D kernel where it is the faster
-// by these estimates.  Both sides measured (split-K against 2-D): down (4096
-// x 12288) at 512 row-major rows 240 and 63 us, at 64 rows 49 and 34; gate/up
-// (12288 x 4096) at 128 row-major rows 104 and 68, packed 68 and 70; 1024 x
-// 1024 at 512 row-major rows 13 and 18.  A decoder layer of 192 rows took 273
-// and 230 us, one of 128 rows 214 and 240 (all four products either way).
-GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp,
-                   bool split_store = false) {
-  const GemmPlan rows = rows_plan(M, N, K, epi, split_store);
+// Row-major activations of more than 32 rows take the 2-D kernel where it is
+// the faster by these estimates.  Both sides measured (split-K against 2-D):
+// down (4096 x 12288) at 512 rows 240 and 63 us, at 64 rows 49 and 34;
+// gate/up (12288 x 4096) at 128 rows 104 and 68; 1024 x 1024 at 512 rows 13
+// and 18.
+GemmPlan linear_plan(int M, int N, int K, int epi) {
+  const GemmPlan rows = rows_plan(M, N, K, epi, false, false);
   // (a group's rows are read through a 32-bit buffer resource)
   if (M <= 32 || K > (1 << 22)) return rows;
   GemmPlan p{};
@@ -1198,7 +1512,6 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp,
   const int S = K / kKStep;
   p.n_nb = N / 32;
   p.n_tt = (M + 32 * k2dTok - 1) / (32 * k2dTok);
-  const bool deferred = xp;
   double best = 0;
   // wk = 1: tiles of 512 features, a stage (one k step) about 1.7 us; wk = 2:
   // 256 features, two steps in about 2.1 us, an even number of steps.  A
@@ -1217,7 +1530,7 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp,
       const double rounds = full <= 1 ? 1 : 0.3 * full + 0.7 * std::ceil(full);
       const double us = 6.5 + rounds * ((S / wk + ks - 1) / ks) *
                                   (wk == 2 ? 2.1 : 1.7) +
-                        partials_us(ks, M, N, deferred);
+                        partials_us(ks, M, N);
       if (p.n_ks > 0 && us >= best) continue;
       best = us;
       p.wk = wk;
@@ -1227,18 +1540,24 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, bool xp,
   }
   if (p.n_ks > 1)
     p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);
-  return best < rows_us(rows, M, N, K, epi, xp, deferred) ? p : rows;
+  return best < rows_us(rows, M, N, K, epi) ? p : rows;
 }
 
-template <int EPI>
-void gemm2d_launch(const Gemm2dArgs& g, bool xp, int wk, dim3 grid,
-                   hipStream_t st) {
-  using Kernel = void (*)(Gemm2dArgs);
-  const Kernel k = wk == 1 ? (xp ? gemm2d_kernel<EPI, true, 1>
-                                 : gemm2d_kernel<EPI, false, 1>)
-                           : (xp ? gemm2d_kernel<EPI, true, 2>
-                                 : gemm2d_kernel<EPI, false, 2>);
-  hipLaunchKernelGGL(k, grid, dim3(kGThreads), 0, st, g);
+using Kernel2d = void (*)(Gemm2dArgs);
+
+Kernel2d kernel2d(const GemmPlan& p, int epi, bool xp) {
+  if (xp)
+    return p.wide            ? gemm2d_packed_wide_kernel
+           : epi == kSwiglu  ? gemm2d_packed_kernel<kSwiglu>
+           : epi == kAddF32  ? gemm2d_packed_kernel<kAddF32>
+                             : gemm2d_packed_kernel<kStoreBf16>;
+  if (p.wk == 1)
+    return epi == kSwiglu   ? gemm2d_kernel<kSwiglu, 1>
+           : epi == kAddF32 ? gemm2d_kernel<kAddF32, 1>
+                            : gemm2d_kernel<kStoreBf16, 1>;
+  return epi == kSwiglu   ? gemm2d_kernel<kSwiglu, 2>
+         : epi == kAddF32 ? gemm2d_kernel<kAddF32, 2>
+                          : gemm2d_kernel<kStoreBf16, 2>;
 }
 
 // Launches the product; with K split, the partials go to `part` and the
@@ -1250,13 +1569,14 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
   if (!x || !w || !out) return WEDLM_E_ARG;
   if (epi != kStoreBf16 && epi != kAddF32 && epi != kSwiglu) return WEDLM_E_ARG;
   if (!gemm_shape_ok(M, N, K) || ldo < N) return WEDLM_E_SHAPE;
-  GemmPlan p = gemm_plan(M, N, K, epi, xp, defer);
+  GemmPlan p = xp ? packed_plan(M, N, K, epi, defer)
+                  : linear_plan(M, N, K, epi);
   if (p.two_d && !xp) {
     // a caller's own arrays: the 2-D kernel needs 16-byte output rows, and a
     // workspace that only holds the split-K kernel's partials (or is not 16-
     // byte aligned) leaves it fewer splits
     const int esz = epi == kAddF32 ? 4 : 2;
-    const GemmPlan r = rows_plan(M, N, K, epi, defer);
+    const GemmPlan r = rows_plan(M, N, K, epi, false, false);
     if (part_bytes < r.part_bytes) return WEDLM_E_WORKSPACE;
     const size_t one = static_cast<size_t>(M) * N * sizeof(float);
     if (reinterpret_cast<uintptr_t>(out) % (4 * esz) != 0 || ldo % 4 != 0) {
@@ -1279,9 +1599,8 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
     g.n_fb = p.n_nb; g.n_ft = p.n_ft; g.n_tt = p.n_tt; g.n_ks = p.n_ks;
     const int64_t grid = 8ll * p.n_tt * p.n_ks * ((p.n_ft + 7) / 8);
     if (grid > (1ll << 30)) return WEDLM_E_SHAPE;
-    if (epi == kSwiglu) gemm2d_launch<kSwiglu>(g, xp, p.wk, dim3(grid), st);
-    else if (epi == kAddF32) gemm2d_launch<kAddF32>(g, xp, p.wk, dim3(grid), st);
-    else gemm2d_launch<kStoreBf16>(g, xp, p.wk, dim3(grid), st);
+    hipLaunchKernelGGL(kernel2d(p, epi, xp), dim3(grid), dim3(kGThreads), 0, st,
+                       g);
     WEDLM_LAUNCH_CHECK();
     if (n_ks_out) *n_ks_out = p.n_ks;
     if (p.n_ks > 1 && epi == kStoreBf16 && !defer) {
@@ -1405,11 +1724,11 @@ Carve carve(const wedlm_model_config* c, int B, int W, int max_prefix_len) {
   const int Mi = static_cast<int>(M);
   // and of the q|k|v product (summed by the q/k norm that reads it)
   k.part_bytes = std::max(
-      std::max(gemm_plan(Mi, c->hidden, c->n_heads * c->head_dim, kAddF32, true)
-                   .part_bytes,
-               gemm_plan(Mi, c->hidden, c->inter, kAddF32, true).part_bytes),
-      gemm_plan(Mi, (c->n_heads + 2 * c->n_kv_heads) * c->head_dim, c->hidden,
-                kStoreBf16, true, true).part_bytes);
+      std::max(packed_plan(Mi, c->hidden, c->n_heads * c->head_dim, kAddF32,
+                           true).part_bytes,
+               packed_plan(Mi, c->hidden, c->inter, kAddF32, true).part_bytes),
+      packed_plan(Mi, (c->n_heads + 2 * c->n_kv_heads) * c->head_dim, c->hidden,
+                  kStoreBf16, true).part_bytes);
   k.part = off; off += up256(k.part_bytes);
   k.x = off;    off += up256(M * Hd * 4);
   const size_t Mp = (M + 31) / 32 * 32;           // packed: whole tiles
@@ -1479,7 +1798,7 @@ extern "C" size_t wedlm_linear_workspace_size(int32_t M, int32_t N,
   if (!gemm_shape_ok(M, N, K) ||
       (epilogue != kStoreBf16 && epilogue != kAddF32 && epilogue != kSwiglu))
     return 0;
-  return gemm_plan(M, N, K, epilogue, false).part_bytes;
+  return linear_plan(M, N, K, epilogue).part_bytes;
 }
 
 extern "C" int wedlm_linear(const uint16_t* x, const uint16_t* w, int32_t M,

@@ -25,7 +25,11 @@ the end every committed cache row against the oracle's keys and values.
 A step captured in a HIP graph and replayed gives the same bits as eager
 steps.
 """
+import functools
+import hashlib
+import json
 import math
+import os
 
 import numpy as np
 import pytest
@@ -485,3 +489,66 @@ def test_qwen3_shaped_layer_against_oracle(B, W):
             assert list(dec.win_tok[b].cpu().numpy()) == exp[b]["win"]
             y[b] += exp[b]["committed"]
     assert compared > 10
+
+
+# ---------------------------------------------------------------------------
+# the decoder's bits
+# ---------------------------------------------------------------------------
+
+# A change of the order in which a product sums its K moves bf16 roundings,
+# which travel through the layers and decide near ties of the greedy token.
+# tests/golden/decoder_bits.json holds what the forward gave (sha256 of each
+# output) before its products were last rewritten, commit 6ae6c8e, on an
+# MI355X with ROCm 7.2.0's compiler; the inputs come from numpy's seeded
+# generators.  A change that is meant to move these bits writes the file anew
+# and says so.
+GOLDEN_BITS = os.path.join(os.path.dirname(__file__), "golden",
+                           "decoder_bits.json")
+BITS_SHAPES = {
+    "tiny2": WL.MODEL_SHAPES["tiny2"],
+    "qwen3_8b_1l": WL.ModelShape("qwen3_8b_1l_v4k", 302, L=1, Hd=4096, Hq=32,
+                                 Hkv=8, D=128, I=12288, V=4096),
+    # more than 8192 features with K = 2048 and 4096: o and down
+    "wide_1l": WL.ModelShape("wide_1l", 303, L=1, Hd=8448, Hq=16, Hkv=2,
+                             D=128, I=4096, V=512),
+}
+# rows: one 32-row block, two, four, the 2-D tiles (three row tiles, two,
+# four with 256-token SwiGLU tiles, a partly filled last one)
+BITS_CASES = [("tiny2", 2, 16), ("tiny2", 5, 31), ("tiny2", 17, 16),
+              ("qwen3_8b_1l", 1, 31), ("qwen3_8b_1l", 2, 24),
+              ("qwen3_8b_1l", 6, 32), ("qwen3_8b_1l", 8, 32),
+              ("qwen3_8b_1l", 13, 31), ("qwen3_8b_1l", 16, 32),
+              ("wide_1l", 1, 32)]
+
+
+@functools.lru_cache(maxsize=1)
+def _bits_weights(name):
+    return WL.model_weights(BITS_SHAPES[name], seed=7)
+
+
+def _forward_digests(name, B, W):
+    """sha256 of each output of one forward over random caches."""
+    ms = BITS_SHAPES[name]
+    rng = np.random.default_rng(B * 100 + W)
+    dec, _ = _decoder(ms, _bits_weights(name), B, W, pages_per_seq=12, T=1.0)
+    dec.k_cache.copy_(_bf(_rand_bf16(rng, tuple(dec.k_cache.shape))))
+    dec.v_cache.copy_(_bf(_rand_bf16(rng, tuple(dec.v_cache.shape))))
+    dec.win_start.copy_(torch.from_numpy(
+        rng.integers(20, 120, B).astype(np.int32)))
+    tok = rng.integers(0, ms.V, (B, W)).astype(np.int32)
+    tok[rng.random((B, W)) < 0.5] = O.MASK
+    dec.win_tok.copy_(torch.from_numpy(tok))
+    dec.forward()
+    torch.cuda.synchronize()
+    assert (dec.attn_status == 0).all()
+    return {k: hashlib.sha256(
+        getattr(dec, k).contiguous().view(torch.uint8).cpu().numpy()
+        .tobytes()).hexdigest()
+        for k in ("perm", "argmax", "entropy", "pmax", "k_win", "v_win")}
+
+
+@pytest.mark.parametrize("name,B,W", BITS_CASES)
+def test_decoder_bits(name, B, W):
+    with open(GOLDEN_BITS) as f:
+        want = json.load(f)[f"{name} {B}x{W}"]
+    assert _forward_digests(name, B, W) == want
