@@ -104,7 +104,8 @@ size_t wedlm_linear_workspace_size(int32_t M, int32_t N, int32_t K,
 
 /*
  * wedlm_linear -- out = x W^T on bf16 MFMA with fp32 accumulation, summed
- * over K in a fixed order (the result does not depend on the run).
+ * over K in an order that the sizes, the epilogue, the bytes of workspace and
+ * the alignment of the arrays fix (the result does not depend on the run).
  *   x [M, K] bf16 row-major, w [rows, K] bf16 packed (wedlm_pack_weights),
  *   out [M, ldo] (ldo >= N);
  *   epilogue WEDLM_EPI_STORE_BF16: rows = N, out bf16;
@@ -113,11 +114,15 @@ size_t wedlm_linear_workspace_size(int32_t M, int32_t N, int32_t K,
  *            WEDLM_EPI_SWIGLU:     rows = 2N (N gate rows, then N up rows),
  *                                  out bf16 = silu(gate) * up.
  *   N a multiple of 32, K a multiple of 64.  x and out must not overlap.
- * workspace: wedlm_linear_workspace_size() bytes (NULL when that is 0):
- * the fp32 partial products of a residual-add product whose K is split over
- * workgroups, summed into out in split order by a second kernel; its
- * contents on entry do not matter.  Two calls that overlap in time must not
- * share a workspace.
+ * workspace: wedlm_linear_workspace_size() bytes (NULL when that is 0): the
+ * fp32 partial products of a residual-add or (above 32 rows) stored product
+ * whose K is split over workgroups, summed into out in split order by a
+ * second kernel; its contents on entry do not matter.  Above 32 rows some
+ * products run with less as well, with fewer splits: a stored one with none
+ * at all.  Two calls that overlap in time must not share a workspace.
+ * The fastest kernel for many rows needs workspace on a 16-byte
+ * boundary, ldo a multiple of 4 and each row of out on a 16-byte (fp32) or
+ * 8-byte (bf16) boundary; others are taken too, by another kernel.
  */
 int wedlm_linear(const uint16_t* x, const uint16_t* w, int32_t M, int32_t N,
                  int32_t K, int32_t epilogue, void* out, int32_t ldo,

@@ -1503,11 +1503,15 @@ double rows_us(const GemmPlan& p, int M, int N, int K, int epi) {
 // down (4096 x 12288) at 512 rows 240 and 63 us, at 64 rows 49 and 34;
 // gate/up (12288 x 4096) at 128 rows 104 and 68; 1024 x 1024 at 512 rows 13
 // and 18.
-GemmPlan linear_plan(int M, int N, int K, int epi) {
+// part_bytes: room for partials, so that a call with less of it than
+// wedlm_linear_workspace_size() asks for has the kernels compared at the
+// splits that it leaves.
+GemmPlan linear_plan(int M, int N, int K, int epi, size_t part_bytes) {
   const GemmPlan rows = rows_plan(M, N, K, epi, false, false);
   // (a group's rows are read through a 32-bit buffer resource)
   if (M <= 32 || K > (1 << 22)) return rows;
   GemmPlan p{};
+  const size_t room = part_bytes / (static_cast<size_t>(M) * N * sizeof(float));
   p.two_d = true;
   const int S = K / kKStep;
   p.n_nb = N / 32;
@@ -1524,7 +1528,7 @@ GemmPlan linear_plan(int M, int N, int K, int epi) {
     const int wgs = n_ft * p.n_tt;
     const int most = epi == kSwiglu ? 1 : std::min(kGemmTargetWgs / wgs, S / 4);
     for (const int ks : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
-      if (ks > 1 && ks > most) break;
+      if (ks > 1 && (ks > most || static_cast<size_t>(ks) > room)) break;
       // a last round that is mostly empty costs most of a whole one
       const double full = static_cast<double>(wgs) * ks / kGemmTargetWgs;
       const double rounds = full <= 1 ? 1 : 0.3 * full + 0.7 * std::ceil(full);
@@ -1569,26 +1573,22 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
   if (!x || !w || !out) return WEDLM_E_ARG;
   if (epi != kStoreBf16 && epi != kAddF32 && epi != kSwiglu) return WEDLM_E_ARG;
   if (!gemm_shape_ok(M, N, K) || ldo < N) return WEDLM_E_SHAPE;
-  GemmPlan p = xp ? packed_plan(M, N, K, epi, defer)
-                  : linear_plan(M, N, K, epi);
-  if (p.two_d && !xp) {
-    // a caller's own arrays: the 2-D kernel needs 16-byte output rows, and a
-    // workspace that only holds the split-K kernel's partials (or is not 16-
-    // byte aligned) leaves it fewer splits
-    const int esz = epi == kAddF32 ? 4 : 2;
+  GemmPlan p;
+  if (xp) {
+    p = packed_plan(M, N, K, epi, defer);
+  } else {
+    // a caller's own arrays: the 2-D kernel moves four outputs or partials
+    // at a time; arrays that are not aligned for that stay with the split-K
+    // kernel
+    auto aligned = [](const void* q, uintptr_t n) {
+      return reinterpret_cast<uintptr_t>(q) % n == 0;
+    };
+    p = linear_plan(M, N, K, epi, part && aligned(part, 16) ? part_bytes : 0);
     const GemmPlan r = rows_plan(M, N, K, epi, false, false);
-    if (part_bytes < r.part_bytes) return WEDLM_E_WORKSPACE;
-    const size_t one = static_cast<size_t>(M) * N * sizeof(float);
-    if (reinterpret_cast<uintptr_t>(out) % (4 * esz) != 0 || ldo % 4 != 0) {
+    if (p.two_d && (r.part_bytes > (part ? part_bytes : 0) ||
+                    ldo % 4 != 0 ||
+                    !aligned(out, epi == kAddF32 ? 16 : 8)))
       p = r;
-    } else if (part_bytes < p.part_bytes) {
-      p.n_ks = std::max<int>(1, static_cast<int>(part_bytes / one));
-      p.part_bytes = p.n_ks > 1 ? p.n_ks * one : 0;
-    }
-    if (p.two_d && reinterpret_cast<uintptr_t>(part) % 16 != 0) {
-      p.n_ks = 1;
-      p.part_bytes = 0;
-    }
   }
   if (p.part_bytes > 0 && (!part || part_bytes < p.part_bytes))
     return WEDLM_E_WORKSPACE;
@@ -1798,7 +1798,7 @@ extern "C" size_t wedlm_linear_workspace_size(int32_t M, int32_t N,
   if (!gemm_shape_ok(M, N, K) ||
       (epilogue != kStoreBf16 && epilogue != kAddF32 && epilogue != kSwiglu))
     return 0;
-  return linear_plan(M, N, K, epilogue).part_bytes;
+  return linear_plan(M, N, K, epilogue, SIZE_MAX).part_bytes;
 }
 
 extern "C" int wedlm_linear(const uint16_t* x, const uint16_t* w, int32_t M,

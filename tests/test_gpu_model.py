@@ -267,6 +267,59 @@ def test_linear_2d_callers_arrays(ldo, shift, ws):
     assert (err <= bound + 2.0 ** -23 * np.abs(ref)).all(), err.max()
 
 
+def _linear_code(x, w, M, N, K, epi, out, ldo, part, size):
+    """The C entry's return code; x, out, part are device addresses."""
+    code = W_().lib().wedlm_linear(x, w, M, N, K, epi, out, ldo, part, size,
+                                   None)
+    torch.cuda.synchronize()
+    return code
+
+
+# without the workspace that its splits need, the 2-D kernel is slower here
+# than the split-K kernel (139 against 80 us): such calls give the bits of
+# the split-K kernel, which an odd row stride forces
+@pytest.mark.parametrize("how", ["no workspace", "workspace of no address"])
+def test_linear_falls_back_to_split_k(how):
+    w = W_()
+    M, N, K = 64, 4096, 12288
+    g = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    wd = w.pack((torch.randn(N, K, generator=g, device=DEV) /
+                 math.sqrt(K)).bfloat16())
+    need = w.wedlm_linear_workspace_size(M, N, K, 0)
+    assert need > 0                                 # 2-D tiles, K split
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    part, size = None, 0 if how == "no workspace" else need
+    xp, wp = x.data_ptr(), wd.data_ptr()
+    odd = torch.zeros(M, N + 1, dtype=torch.bfloat16, device=DEV)
+    out = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
+    full = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
+    assert _linear_code(xp, wp, M, N, K, 0, odd.data_ptr(), N + 1, None, 0) == 0
+    assert _linear_code(xp, wp, M, N, K, 0, out.data_ptr(), N, part, size) == 0
+    assert torch.equal(out.view(torch.int16), odd[:, :N].view(torch.int16))
+    # with its workspace the call takes the other kernel
+    assert _linear_code(xp, wp, M, N, K, 0, full.data_ptr(), N,
+                        ws.data_ptr(), need) == 0
+    assert not torch.equal(full.view(torch.int16), out.view(torch.int16))
+
+
+def test_linear_refuses_what_it_refused():
+    """A residual add whose split-K plan needs a workspace is refused without
+    one, with less than that, and with a size but no address
+    (WEDLM_E_WORKSPACE)."""
+    w = W_()
+    M, N, K = 64, 1024, 8192
+    need = 2 * M * N * 4            # two splits would do for neither kernel
+    x = torch.zeros(M, K, dtype=torch.bfloat16, device=DEV)
+    wd = torch.zeros(N, K, dtype=torch.bfloat16, device=DEV)
+    out = torch.zeros(M, N, device=DEV)
+    ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
+    for part, size in ((None, 0), (None, 1 << 30), (ws.data_ptr(), need)):
+        assert _linear_code(x.data_ptr(), wd.data_ptr(), M, N, K, 1,
+                            out.data_ptr(), N, part, size) == -3
+    assert not out.any()
+
+
 def test_linear_split_workspace_reuse():
     """Products that split K over workgroups (residual add at N = 4096) share
     one workspace back to back with products that do not."""
