@@ -120,8 +120,8 @@ size_t wedlm_linear_workspace_size(int32_t M, int32_t N, int32_t K,
  * second kernel; its contents on entry do not matter.  Above 32 rows some
  * products run with less as well, with fewer splits: a stored one with none
  * at all.  Two calls that overlap in time must not share a workspace.
- * The fastest kernel for many rows needs workspace on a 16-byte
- * boundary, ldo a multiple of 4 and each row of out on a 16-byte (fp32) or
+ * The fastest kernel for many rows needs x and workspace on 16-byte
+ * boundaries, ldo a multiple of 4 and each row of out on a 16-byte (fp32) or
  * 8-byte (bf16) boundary; others are taken too, by another kernel.
  */
 int wedlm_linear(const uint16_t* x, const uint16_t* w, int32_t M, int32_t N,

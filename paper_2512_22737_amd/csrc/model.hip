@@ -1577,16 +1577,16 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
   if (xp) {
     p = packed_plan(M, N, K, epi, defer);
   } else {
-    // a caller's own arrays: the 2-D kernel moves four outputs or partials
-    // at a time; arrays that are not aligned for that stay with the split-K
-    // kernel
+    // a caller's own arrays: the 2-D kernel moves 16 bytes of x into LDS, and
+    // four outputs or partials, at a time; arrays that are not aligned for
+    // that stay with the split-K kernel
     auto aligned = [](const void* q, uintptr_t n) {
       return reinterpret_cast<uintptr_t>(q) % n == 0;
     };
     p = linear_plan(M, N, K, epi, part && aligned(part, 16) ? part_bytes : 0);
     const GemmPlan r = rows_plan(M, N, K, epi, false, false);
     if (p.two_d && (r.part_bytes > (part ? part_bytes : 0) ||
-                    ldo % 4 != 0 ||
+                    !aligned(x, 16) || ldo % 4 != 0 ||
                     !aligned(out, epi == kAddF32 ? 16 : 8)))
       p = r;
   }

@@ -276,31 +276,35 @@ def _linear_code(x, w, M, N, K, epi, out, ldo, part, size):
 
 
 # without the workspace that its splits need, the 2-D kernel is slower here
-# than the split-K kernel (139 against 80 us): such calls give the bits of
-# the split-K kernel, which an odd row stride forces
-@pytest.mark.parametrize("how", ["no workspace", "workspace of no address"])
+# than the split-K kernel (139 against 80 us), and rows that are not on
+# 16-byte boundaries it does not take: such calls give the bits of the
+# split-K kernel, which an odd row stride forces
+@pytest.mark.parametrize("how", ["no workspace", "x", "workspace of no address"])
 def test_linear_falls_back_to_split_k(how):
     w = W_()
     M, N, K = 64, 4096, 12288
     g = torch.Generator(device=DEV).manual_seed(3)
-    x = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    x = torch.randn(M * K + 4, generator=g, device=DEV).bfloat16()
+    at = 4 if how == "x" else 0                     # 8 bytes off
     wd = w.pack((torch.randn(N, K, generator=g, device=DEV) /
                  math.sqrt(K)).bfloat16())
     need = w.wedlm_linear_workspace_size(M, N, K, 0)
     assert need > 0                                 # 2-D tiles, K split
     ws = torch.empty(need, dtype=torch.uint8, device=DEV)
-    part, size = None, 0 if how == "no workspace" else need
-    xp, wp = x.data_ptr(), wd.data_ptr()
+    part, size = {"no workspace": (None, 0), "x": (ws.data_ptr(), need),
+                  "workspace of no address": (None, need)}[how]
+    xp, wp = x.data_ptr() + 2 * at, wd.data_ptr()
     odd = torch.zeros(M, N + 1, dtype=torch.bfloat16, device=DEV)
     out = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
     full = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
     assert _linear_code(xp, wp, M, N, K, 0, odd.data_ptr(), N + 1, None, 0) == 0
     assert _linear_code(xp, wp, M, N, K, 0, out.data_ptr(), N, part, size) == 0
     assert torch.equal(out.view(torch.int16), odd[:, :N].view(torch.int16))
-    # with its workspace the call takes the other kernel
-    assert _linear_code(xp, wp, M, N, K, 0, full.data_ptr(), N,
-                        ws.data_ptr(), need) == 0
-    assert not torch.equal(full.view(torch.int16), out.view(torch.int16))
+    # with aligned arrays and its workspace the call takes the other kernel
+    if how != "x":
+        assert _linear_code(xp, wp, M, N, K, 0, full.data_ptr(), N,
+                            ws.data_ptr(), need) == 0
+        assert not torch.equal(full.view(torch.int16), out.view(torch.int16))
 
 
 def test_linear_refuses_what_it_refused():
