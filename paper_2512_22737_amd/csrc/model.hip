@@ -653,33 +653,44 @@ __global__ __launch_bounds__(kGThreads) void gemm_persistent_kernel(
 // x[t][n] += sum over splits k (in order) of part[k][t][n]; a thread takes
 // four consecutive n (N a multiple of 32), as one 16-byte access each where
 // the caller's rows allow it (VEC: x and part on 16-byte boundaries, ldx a
-// multiple of 4)
+// multiple of 4), and loads four splits at a time (past the last one: it
+// again)
 template <bool VEC>
 __global__ __launch_bounds__(256) void add_partials_kernel(
     float* __restrict__ x, int ldx, const float* __restrict__ part, int n_ks,
     int M, int N) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t n4 = N / 4;
-  if (i >= M * n4) return;
-  const int64_t t = i / n4;
+  const int n4 = N / 4;
+  const int64_t total = static_cast<int64_t>(M) * n4;
+  if (i >= total) return;
+  // (a 64-bit division costs as much as the loads)
+  const int64_t t = total <= 0x7fffffff
+                        ? static_cast<uint32_t>(i) / static_cast<uint32_t>(n4)
+                        : i / n4;
   const int n = static_cast<int>(i - t * n4) * 4;
+  auto load = [](const float* p) {
+    if constexpr (VEC) return *reinterpret_cast<const floatx4_t*>(p);
+    else return floatx4_t{p[0], p[1], p[2], p[3]};
+  };
   float* const xp = x + t * ldx + n;
   const float* const pp = part + t * N + n;
   const int64_t ps = static_cast<int64_t>(M) * N;
-  if constexpr (VEC) {
-    floatx4_t v = *reinterpret_cast<const floatx4_t*>(xp);
-    for (int k = 0; k < n_ks; ++k) {
-      const floatx4_t p = *reinterpret_cast<const floatx4_t*>(pp + k * ps);
+  floatx4_t v = load(xp);
+  for (int k = 0; k < n_ks; k += 4) {
+    floatx4_t p[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] += p[r];
-    }
+    for (int j = 0; j < 4; ++j) p[j] = load(pp + min(k + j, n_ks - 1) * ps);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (k + j < n_ks)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] += p[j][r];
+  }
+  if constexpr (VEC) {
     *reinterpret_cast<floatx4_t*>(xp) = v;
   } else {
-    for (int r = 0; r < 4; ++r) {
-      float v = xp[r];
-      for (int k = 0; k < n_ks; ++k) v += pp[k * ps + r];
-      xp[r] = v;
-    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xp[r] = v[r];
   }
 }
 
@@ -699,8 +710,9 @@ void add_partials(float* x, int ldx, const float* part, int n_ks, int M, int N,
 
 // ---------------------------------------------------------------------------
 // 2-D tiled GEMM of the decoder's packed activations (k2pMinRows rows and
-// more: batches of windows).  A workgroup computes 256 features (8 blocks; for SwiGLU 4 gate blocks and
-// their 4 up blocks) x 128 tokens (4 row tiles) over its run of K steps.
+// more: batches of windows).  A workgroup computes 256 features (8 blocks;
+// for SwiGLU 4 gate blocks and their 4 up blocks) x 128 tokens (4 row tiles)
+// over its run of K steps.
 // Per 64-wide step the 12 packed 4 KB tiles (8 weight, 4 activation) go
 // from HBM into LDS as they are, with LDS-destination buffer loads (the
 // packed layout is already the MFMA operand order, so every fragment read

@@ -267,6 +267,31 @@ def test_linear_2d_callers_arrays(ldo, shift, ws):
     assert (err <= bound + 2.0 ** -23 * np.abs(ref)).all(), err.max()
 
 
+# partials added four values (ldo a multiple of 4) and one at a time, four
+# splits loaded at once: 2, 5 and 7 splits, one row and a ragged 32
+@pytest.mark.parametrize("M,N,K", [(32, 4096, 4096), (31, 1600, 4608),
+                                   (1, 1152, 4224), (29, 1152, 4608)])
+def test_linear_partials(M, N, K):
+    w = W_()
+    assert w.wedlm_linear_workspace_size(M, N, K, 1) > M * N * 4
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    x = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    wt = (torch.randn(N, K, generator=g, device=DEV) / math.sqrt(K)).bfloat16()
+    base = torch.randn(M, N, generator=g, device=DEV)
+    outs = []
+    for ldo in (N, N + 4, N + 1):
+        out = torch.zeros(M, ldo, device=DEV)
+        out[:, :N] = base
+        w.wedlm_linear(x, w.pack(wt), 1, out)
+        assert not out[:, N:].any()
+        outs.append(out[:, :N].clone())
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    xf, wf = x.cpu().double(), wt.cpu().double()
+    ref = base.cpu().double() + xf @ wf.T
+    bound = K * 2.0 ** -24 * (xf.abs() @ wf.abs().T) + 2.0 ** -23 * ref.abs()
+    assert ((outs[0].cpu().double() - ref).abs() <= bound).all()
+
+
 def _linear_code(x, w, M, N, K, epi, out, ldo, part, size):
     """The C entry's return code; x, out, part are device addresses."""
     code = W_().lib().wedlm_linear(x, w, M, N, K, epi, out, ldo, part, size,
