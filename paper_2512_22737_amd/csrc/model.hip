@@ -1075,12 +1075,13 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_kernel(Gemm2dArgs a) {
   static_assert(k2dRing >= k2dLead + 1 && k2dLead >= 2, "slot reuse");
   static_assert(WK == 1 || k2dRing * kStage >= kGWaves * 16384, "exchange");
   __shared__ __attribute__((aligned(1024))) char lds2[k2dRing * kStage];
-  // tile order: the K splits and row tiles of one feature tile on one XCD
+  // tile order: the row tiles of one K split of one feature tile on one XCD
+  // (they share its weights); the splits spread over the XCDs, as products of
+  // few feature tiles have no other way to reach all eight
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int per_ft = a.n_tt * a.n_ks;
-  const int ft = xcd + 8 * (local / per_ft);
-  const int tt = (local % per_ft) / a.n_ks;
-  const int ks = local % a.n_ks;
+  const int u = xcd + 8 * (local / a.n_tt);
+  const int ft = u / a.n_ks, ks = u % a.n_ks;
+  const int tt = local % a.n_tt;
   if (ft >= a.n_ft) return;                          // whole workgroup
 
   const int lane = lane_id();
@@ -1609,7 +1610,9 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
     g.x = x; g.w = w; g.out = out; g.part = static_cast<float*>(part);
     g.M = M; g.N = N; g.K = K; g.ldo = ldo;
     g.n_fb = p.n_nb; g.n_ft = p.n_ft; g.n_tt = p.n_tt; g.n_ks = p.n_ks;
-    const int64_t grid = 8ll * p.n_tt * p.n_ks * ((p.n_ft + 7) / 8);
+    const int64_t grid =
+        xp ? 8ll * p.n_tt * p.n_ks * ((p.n_ft + 7) / 8)
+           : 8ll * p.n_tt * ((static_cast<int64_t>(p.n_ft) * p.n_ks + 7) / 8);
     if (grid > (1ll << 30)) return WEDLM_E_SHAPE;
     hipLaunchKernelGGL(kernel2d(p, epi, xp), dim3(grid), dim3(kGThreads), 0, st,
                        g);

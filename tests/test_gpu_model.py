@@ -215,6 +215,8 @@ LINEAR_2D_CASES = [
     (130, 2080, 2048, 0), (130, 2080, 2048, 1), (257, 4128, 2048, 2),
     (1000, 4128, 1088, 1), (1000, 4128, 1088, 0), (300, 4128, 1088, 2),
     (513, 4096, 256, 0), (64, 1056, 4096, 0),
+    # one feature tile, split over the XCDs
+    (33, 32, 4096, 0), (200, 32, 1664, 0), (706, 256, 5248, 1),
 ]
 
 
