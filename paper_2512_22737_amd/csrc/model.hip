@@ -1491,31 +1491,52 @@ GemmPlan packed_plan(int M, int N, int K, int epi, bool split_store) {
   return p;
 }
 
-// Estimates of a product's time in microseconds, row-major activations,
-// fitted to products of 33 to 1024 rows, N 512 to 12288 and K 1024 to 12288.
-// Partials are written and read at 4.5 TB/s, the launch that sums them takes
-// 4 us.
-double partials_us(int n_ks, int M, int N) {
-  return n_ks <= 1 ? 0 : 8e-6 / 4.5 * n_ks * M * N + 4;
-}
+// Estimates of a product's time in microseconds, row-major activations.  The
+// constants were chosen on 2324 products (33 to 1024 rows, N 128 to 12288, K
+// 256 to 12288, all three epilogues), each timed with the split-K kernel and
+// with every 2-D candidate: by what the choice costs against the fastest of
+// them, a choice that loses to the split-K kernel counting four times.
+// Workgroups are counted per XCD of 32 CUs, where the kernels put them; a
+// round of them moves its steps at the rate that the filled CUs share.
 
-// The split-K kernel: a round of one workgroup per CU runs S / (8 n_ks) steps
-// of NA * NB MFMA groups per wave (its lanes read 64 bytes of 32 rows of
-// activations per load).
+// The split-K kernel: S / (8 n_ks) steps per wave and round, by its rows per
+// group (the rows of a partly filled last group re-read one row) and weight
+// blocks.
 double rows_us(const GemmPlan& p, int M, int N, int K, int epi) {
-  const double rounds =
-      std::max(1.0, static_cast<double>(p.n_nb) * p.n_rg * p.n_ks / kGemmTargetWgs);
-  const int steps = (K / kKStep + p.nw * p.n_ks - 1) / (p.nw * p.n_ks);
-  const int groups = p.nb * (epi == kSwiglu ? 2 : 1);
-  return 1.5 + rounds * steps * (1.6 + 0.9 * groups) +
-         partials_us(p.n_ks, M, N);
+  const double full = (p.n_nb + 7) / 8 * static_cast<double>(p.n_rg) * p.n_ks / 32;
+  const double rounds = full <= 1 ? 1 : 0.2 * full + 0.8 * std::ceil(full);
+  const double steps = static_cast<double>(K) / kKStep / (p.nw * p.n_ks);
+  const double fill = std::min(1.0, full);
+  const double per_step = p.nb == 4        ? 3.9 + 0.85 * fill
+                          : epi == kSwiglu ? 2.7 + 0.6 * fill
+                                           : 2.2 + 1.05 * fill;
+  const double live = static_cast<double>(M) / (32 * p.nb) / p.n_rg;
+  return 1.8 + rounds * (2.2 + steps * per_step * (0.4 + 0.6 * live)) +
+         (p.n_ks > 1 ? 1.75 + 1.2e-6 * p.n_ks * M * N : 0.0);
 }
 
-// Row-major activations of more than 32 rows take the 2-D kernel where it is
-// the faster by these estimates.  Both sides measured (split-K against 2-D):
-// down (4096 x 12288) at 512 rows 240 and 63 us, at 64 rows 49 and 34;
-// gate/up (12288 x 4096) at 128 rows 104 and 68; 1024 x 1024 at 512 rows 13
-// and 18.
+// The 2-D kernel: a stage is one k step of 512 features (wk = 1) or two of
+// 256 (wk = 2).
+constexpr double k2dStart = 3.7, k2dRound = 5.8;
+double tiles_us(int wk, int n_ft, int n_tt, int n_ks, int M, int N, int K) {
+  const double full = (n_ft * n_ks + 7) / 8 * static_cast<double>(n_tt) / 32;
+  const int stages = (K / kKStep / wk + n_ks - 1) / n_ks;
+  const double fill = std::min(1.0, full);
+  return k2dStart +
+         std::max(1.0, std::ceil(full)) *
+             (k2dRound +
+              stages * (wk == 2 ? 1.15 + 0.4 * fill : 1.3 + 0.25 * fill)) +
+         (n_ks > 1 ? 1.05 + 1.2e-6 * n_ks * M * N : 0.0);
+}
+
+// Row-major activations of more than 32 rows take the 2-D kernel where its
+// estimate is 6% below the split-K kernel's.  Of the 2324 products 922 do;
+// six of them are more than 2% slower than with the split-K kernel, at most
+// 6%, and over all the choice is 0.7% from the fastest.  Both sides measured
+// (split-K against 2-D): down (4096 x 12288) at 512 rows 240 and 63 us, at 64
+// rows 49 and 33; gate/up (12288 x 4096) at 128 rows 104 and 66; o (4096 x
+// 4096) at 40 rows 17.8 and 19.5, at 128 rows 35.6 and 23.0; 1024 x 1024 at
+// 512 rows 15 and 18.
 // part_bytes: room for partials, so that a call with less of it than
 // wedlm_linear_workspace_size() asks for has the kernels compared at the
 // splits that it leaves.
@@ -1523,41 +1544,38 @@ GemmPlan linear_plan(int M, int N, int K, int epi, size_t part_bytes) {
   const GemmPlan rows = rows_plan(M, N, K, epi, false, false);
   // (a group's rows are read through a 32-bit buffer resource)
   if (M <= 32 || K > (1 << 22)) return rows;
+  double best = 0.94 * rows_us(rows, M, N, K, epi);
+  if (best <= k2dStart + k2dRound) return rows;
   GemmPlan p{};
-  const size_t room = part_bytes / (static_cast<size_t>(M) * N * sizeof(float));
   p.two_d = true;
   const int S = K / kKStep;
   p.n_nb = N / 32;
   p.n_tt = (M + 32 * k2dTok - 1) / (32 * k2dTok);
-  double best = 0;
-  // wk = 1: tiles of 512 features, a stage (one k step) about 1.7 us; wk = 2:
-  // 256 features, two steps in about 2.1 us, an even number of steps.  A
-  // residual-add or stored product splits K (at least four steps per split)
-  // while its tiles fill less than one round of the CUs.
+  const size_t room = part_bytes / (static_cast<size_t>(M) * N * sizeof(float));
+  // two waves per feature group need an even number of steps; one is for the
+  // others and for SwiGLU.  A residual-add or stored product splits K (at
+  // least four steps per split) while its tiles fill less than one round of
+  // the CUs.
   for (int wk = 1; wk <= 2; ++wk) {
     if (wk == 2 ? S % 2 != 0 : S % 2 == 0 && epi != kSwiglu) continue;
     const int per = kGWaves / wk * (epi == kSwiglu ? 1 : 2);
     const int n_ft = (p.n_nb + per - 1) / per;
-    const int wgs = n_ft * p.n_tt;
-    const int most = epi == kSwiglu ? 1 : std::min(kGemmTargetWgs / wgs, S / 4);
+    const int most = epi == kSwiglu
+                         ? 1 : std::min(kGemmTargetWgs / (n_ft * p.n_tt), S / 4);
     for (const int ks : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
       if (ks > 1 && (ks > most || static_cast<size_t>(ks) > room)) break;
-      // a last round that is mostly empty costs most of a whole one
-      const double full = static_cast<double>(wgs) * ks / kGemmTargetWgs;
-      const double rounds = full <= 1 ? 1 : 0.3 * full + 0.7 * std::ceil(full);
-      const double us = 6.5 + rounds * ((S / wk + ks - 1) / ks) *
-                                  (wk == 2 ? 2.1 : 1.7) +
-                        partials_us(ks, M, N);
-      if (p.n_ks > 0 && us >= best) continue;
+      const double us = tiles_us(wk, n_ft, p.n_tt, ks, M, N, K);
+      if (us >= best) continue;
       best = us;
       p.wk = wk;
       p.n_ft = n_ft;
       p.n_ks = ks;
     }
   }
+  if (p.n_ks == 0) return rows;
   if (p.n_ks > 1)
     p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);
-  return best < rows_us(rows, M, N, K, epi) ? p : rows;
+  return p;
 }
 
 using Kernel2d = void (*)(Gemm2dArgs);
@@ -1813,7 +1831,9 @@ extern "C" size_t wedlm_linear_workspace_size(int32_t M, int32_t N,
   if (!gemm_shape_ok(M, N, K) ||
       (epilogue != kStoreBf16 && epilogue != kAddF32 && epilogue != kSwiglu))
     return 0;
-  return linear_plan(M, N, K, epilogue, SIZE_MAX).part_bytes;
+  // enough for either kernel: which of the two runs depends on the arrays too
+  return std::max(linear_plan(M, N, K, epilogue, SIZE_MAX).part_bytes,
+                  rows_plan(M, N, K, epilogue, false, false).part_bytes);
 }
 
 extern "C" int wedlm_linear(const uint16_t* x, const uint16_t* w, int32_t M,

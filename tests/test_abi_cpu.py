@@ -56,6 +56,27 @@ def test_version_and_strerror():
     assert lib.wedlm_strerror(12345) == b"unknown error code"
 
 
+# The splits that wedlm_linear's plan asks room for tell its kernels apart:
+# products measured with both, in us with the split-K kernel and the 2-D
+# tiles, row-major activations
+@pytest.mark.parametrize("M,N,K,epi,splits", [
+    (33, 4096, 4096, 1, 2),         # 16.9, 19.3 (16 splits)
+    (40, 4096, 4096, 1, 2),         # 17.9, 19.5
+    (65, 2048, 6144, 1, 4),         # 16.9, 19.8
+    (130, 2080, 2048, 1, 0),        # about 13, 18
+    (64, 4096, 12288, 1, 16),       # 49, 33
+    (128, 4096, 4096, 1, 8),        # 35.6, 23.4
+    (512, 4096, 12288, 1, 4),       # 250, 61
+    (64, 4096, 12288, 0, 16),       # 81, 33
+    (1024, 1024, 1024, 0, 0),       # either way
+    (32, 4096, 12288, 1, 2),        # up to 32 rows: split-K
+    (32, 4096, 12288, 0, 0),
+])
+def test_linear_plan(M, N, K, epi, splits):
+    assert _lib().wedlm_linear_workspace_size(M, N, K, epi) == \
+        splits * M * N * 4
+
+
 def _fake():
     # a non-null address that is never dereferenced: validation fails first
     return ctypes.c_void_p(0x1000)

@@ -206,23 +206,46 @@ def test_linear(M, N, K, epi):
         assert (err <= tol).all(), err.max()
 
 
-# sizes whose products go through the 2-D tiles: one row and one feature
-# block past a tile (130 = 128 + 2 rows, 2080 = 8 x 256 + 32 features), K
-# split over workgroups, an odd number of k steps (K = 17 x 64: the tiles of
-# 512 features), several row tiles, and a single split
+# sizes whose products go through the 2-D tiles: a few rows, feature blocks
+# and row tiles past a tile (130 = 128 + 2 rows, 4128 = 16 x 256 + 32
+# features), one feature block alone, several row tiles; by the waves per
+# feature group (one: an odd number of k steps or many SwiGLU tiles) the
+# stages of a split, where a run of 1 to 3 is the tail of the loop by fours
 LINEAR_2D_CASES = [
     # M, N, K, epilogue
-    (130, 2080, 2048, 0), (130, 2080, 2048, 1), (257, 4128, 2048, 2),
-    (1000, 4128, 1088, 1), (1000, 4128, 1088, 0), (300, 4128, 1088, 2),
+    (257, 4128, 2048, 2), (1000, 4128, 1088, 1), (1000, 4128, 1088, 0),
     (513, 4096, 256, 0), (64, 1056, 4096, 0),
-    # one feature tile, split over the XCDs
-    (33, 32, 4096, 0), (200, 32, 1664, 0), (706, 256, 5248, 1),
+    # two waves per group: 2; 2 and 3; 3 and 4; 4 and 5; 5 and 6 stages
+    (33, 32, 4096, 0), (200, 32, 1664, 0), (1000, 1056, 1280, 1),
+    (33, 6176, 6144, 0), (130, 4128, 4096, 1),
+    # 2 and 3 stages, not split
+    (200, 6176, 256, 2), (257, 6176, 384, 1),
+    # one wave per group: 4 and 5; 5 and 6; 6 and 7 stages; 4 and 7, not split
+    (96, 32, 2624, 0), (64, 4128, 4160, 1), (257, 4128, 1728, 0),
+    (513, 6176, 256, 2), (300, 6176, 448, 2),
+    # fewer splits than the split-K kernel would take (and want room for)
+    (280, 32, 11392, 1),
+    # beside the line: these stay with the split-K kernel
+    (130, 2080, 2048, 0), (130, 2080, 2048, 1), (300, 4128, 1088, 2),
 ]
 
 
 @pytest.mark.parametrize("M,N,K,epi", LINEAR_2D_CASES)
 def test_linear_2d(M, N, K, epi):
     test_linear(M, N, K, epi)
+    # an odd row stride forces the split-K kernel, which sums in another order
+    w = W_()
+    g = torch.Generator(device=DEV).manual_seed(N + K)
+    x = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    wt = torch.randn(2 * N if epi == 2 else N, K, generator=g, device=DEV)
+    wd = w.pack((wt / math.sqrt(K)).bfloat16())
+    dt = torch.float32 if epi == 1 else torch.bfloat16
+    even = torch.zeros(M, N, dtype=dt, device=DEV)
+    odd = torch.zeros(M, N + 1, dtype=dt, device=DEV)
+    w.wedlm_linear(x, wd, epi, even)
+    w.wedlm_linear(x, wd, epi, odd)
+    two_d = (M, N, K, epi) not in LINEAR_2D_CASES[-3:]
+    assert torch.equal(even, odd[:, :N]) == (not two_d)
 
 
 # the persistent form of up to 32 rows: more 32-feature blocks than CUs (257:
@@ -238,11 +261,11 @@ def test_linear_persistent(M, N, K, epi):
 # what the split-K kernel took, the 2-D tiles take or leave to it: a residual
 # add with no workspace (a single split), with rows that are not on 16-byte
 # boundaries and with an odd row stride
-@pytest.mark.parametrize("ldo,shift,ws", [(2080, 0, 0), (2080, 1, 1),
-                                          (2083, 0, 1), (2084, 0, 2)])
+@pytest.mark.parametrize("ldo,shift,ws", [(4128, 0, 0), (4128, 1, 1),
+                                          (4131, 0, 1), (4132, 0, 2)])
 def test_linear_2d_callers_arrays(ldo, shift, ws):
     w = W_()
-    M, N, K = 130, 2080, 2048
+    M, N, K = 130, 4128, 4096
     rng = np.random.default_rng(ldo + shift)
     x = _rand_bf16(rng, (M, K))
     wt = _rand_bf16(rng, (N, K), 1.0 / math.sqrt(K))
