@@ -563,9 +563,11 @@ __global__ __launch_bounds__(NW * kWave) void gemm_kernel(GemmArgs a) {
 // activations are read from L2 once per workgroup instead of once per block
 // (row-major ones 64 bytes of 32 rows at a time).  The waves' sums of a block
 // meet in one of two LDS buffers, in wave order, with one barrier per block:
-// the same bits as the plain form.  Bound by the weight stream: gate/up (201
-// MB) at 32 row-major rows 50 -> 41 us, at 16 43 -> 38, at one 39 -> 36; a
-// decoder step of one window, 8 layers, 1236 -> 1197 us with packed ones.
+// for stored and SwiGLU products the same bits as the plain form (which takes
+// residual adds of K up to 4096 in four waves and one or two splits).  Bound
+// by the weight stream: gate/up (201 MB) at 32 row-major rows 50 -> 41 us, at
+// 16 43 -> 38, at one 39 -> 36; a decoder step of one window, 8 layers, 1236
+// -> 1197 us with packed ones.
 // (K split three ways, down at one row took 23 us against 21.)
 // ---------------------------------------------------------------------------
 template <int NA, int SPW, int EPI, bool XP>
@@ -1416,6 +1418,31 @@ constexpr int k2pMinRows = 256;
 // CUs; at 96 or 128 workgroups the 128-token tiles measured faster)
 constexpr int kWideMinWgs = 3 * kGemmTargetWgs / 4;
 
+// Whether the persistent form is the faster one: the blocks go in as few
+// rounds as of one workgroup per CU, each workgroup taking the same number of
+// them, where the plain form keeps two workgroups on a CU.  It loses where
+// its rounds are few and full and there are few activations to read again.
+// Measured (plain against persistent), N 8224 to 32768, 1 to 32 rows:
+//   stored products   faster throughout (K 2048 at one row, N 16384 15.4 and
+//                     15.0 us)
+//   residual adds     K 4096 faster throughout; K 2048 at one row N 10240
+//                     11.3 and 10.8, N 16384 13.4 and 15.3.  The decoder's
+//                     (hidden above 8192) keep the plain form, whose sums go
+//                     in another order: two splits of four waves, for eight
+//                     waves and one add
+//   SwiGLU, packed    two full rounds lose (4096 x 16384 46 and 49), three
+//                     are even (24576), others gain
+//   SwiGLU, row-major 4096 x 16384 at one row 45.4 and 47.6, at 32 rows 52.8
+//                     and 51.1; 2048 x 14336 at one row 22.9 and 23.9; 4096 x
+//                     12288 39.0 and 36.6
+bool persistent_pays(int M, int n_nb, int rounds, int spw, int epi, bool xp) {
+  const double fill = static_cast<double>(n_nb) / (rounds * kGemmTargetWgs);
+  if (epi == kStoreBf16) return true;
+  if (epi == kAddF32) return !xp && (spw == 8 || M >= 20 || fill <= 0.67);
+  if (xp) return rounds > 2 || fill <= 0.9;
+  return M >= 24 || fill <= 0.8 || rounds >= 4 || (rounds == 3 && spw == 8);
+}
+
 // The plan of the split-K kernel (few rows).
 GemmPlan rows_plan(int M, int N, int K, int epi, bool xp, bool split_store) {
   GemmPlan p{};
@@ -1436,18 +1463,16 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool xp, bool split_store) {
     const int wgs = p.n_nb * p.n_rg;
     p.n_ks = std::max(1, std::min(kGemmTargetWgs / wgs, K / kKStep / kGWaves));
   }
-  // the persistent form: the blocks in as few rounds as of one workgroup per
-  // CU, each workgroup taking the same number of them.  Not for the decoder's
-  // residual adds (hidden above 8192), whose sums it would take in another
-  // order: eight waves, then one add, for two or four waves per split
   const int spw = K / kKStep / kGWaves;
   if (p.nb == 1 && p.n_nb > kGemmTargetWgs && K % (kKStep * kGWaves) == 0 &&
-      (spw == 8 || spw == 4) && !(xp && epi == kAddF32)) {
+      (spw == 8 || spw == 4)) {
     const int rounds = (p.n_nb + kGemmTargetWgs - 1) / kGemmTargetWgs;
-    p.spw = spw;
-    p.nw = kGWaves;
-    p.n_ks = 1;
-    p.wgs = (p.n_nb + rounds - 1) / rounds;
+    if (persistent_pays(M, p.n_nb, rounds, spw, epi, xp)) {
+      p.spw = spw;
+      p.nw = kGWaves;
+      p.n_ks = 1;
+      p.wgs = (p.n_nb + rounds - 1) / rounds;
+    }
   }
   if (p.n_ks > 1)
     p.part_bytes = static_cast<size_t>(p.n_ks) * M * N * sizeof(float);

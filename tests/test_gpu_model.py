@@ -258,6 +258,36 @@ def test_linear_persistent(M, N, K, epi):
     test_linear(M, N, K, epi)
 
 
+# the bits of a feature do not depend on how many are computed: up to 8192 of
+# them (4096 with their up rows) the plain form runs.  Residual adds alone
+# differ where the persistent form takes them, which it does not from the
+# row and block counts on at which it is the slower one (at K 2048)
+@pytest.mark.parametrize("M,N,K,epi,same", [
+    (1, 8224, 4096, 0, True), (32, 12320, 2048, 0, True),
+    (1, 8224, 2048, 2, True), (31, 12288, 4096, 2, True),
+    (9, 16384, 4096, 2, True), (32, 12288, 2048, 1, False),
+    (1, 12288, 2048, 1, True), (19, 16384, 2048, 1, True),
+    (1, 12288, 4096, 1, False)])
+def test_linear_same_bits_as_the_plain_form(M, N, K, epi, same):
+    w = W_()
+    g = torch.Generator(device=DEV).manual_seed(N + K + M)
+    x = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    up = 2 if epi == 2 else 1
+    wt = (torch.randn(up, N, K, generator=g, device=DEV) /
+          math.sqrt(K)).bfloat16()
+    dt = torch.float32 if epi == 1 else torch.bfloat16
+    base = torch.randn(M, N, generator=g, device=DEV).to(dt)
+    whole = base.clone()
+    w.wedlm_linear(x, w.pack(wt.reshape(up * N, K)), epi, whole)
+    parts = []
+    for a in range(0, N, 4096):
+        out = base[:, a:a + 4096].contiguous()
+        part = wt[:, a:a + 4096].reshape(-1, K).contiguous()
+        w.wedlm_linear(x, w.pack(part), epi, out)
+        parts.append(out)
+    assert torch.equal(whole, torch.cat(parts, 1)) == same
+
+
 # what the split-K kernel took, the 2-D tiles take or leave to it: a residual
 # add with no workspace (a single split), with rows that are not on 16-byte
 # boundaries and with an odd row stride
