@@ -577,11 +577,13 @@ def test_decoder_graph_replay_matches_eager():
     assert torch.equal(v0.view(torch.int16), v1.view(torch.int16))
 
 
-@pytest.mark.parametrize("B,W", [(2, 32), (8, 32), (16, 32), (13, 31)])
+@pytest.mark.parametrize("B,W", [(1, 32), (1, 31), (2, 32), (8, 32), (16, 32),
+                                 (13, 31)])
 def test_qwen3_shaped_layer_against_oracle(B, W):
     """One layer at the Qwen3-8B sizes (hidden 4096, 32/8 heads of 128, MLP
-    12288; vocabulary cut to 4096), B sequences of W slots: 64 rows (the
-    split-K products, the RMSNorms summing split partials), 256 rows (the
+    12288; vocabulary cut to 4096), B sequences of W slots: 32 or 31 rows (the
+    gate/up product in its persistent form), 64 rows (the split-K products,
+    the RMSNorms summing split partials), 256 rows (the
     2-D tiled products, o's input packed, residual-add products split over
     8 workgroups), 512 rows (the gate/up product in 256-token tiles) or 403
     rows (those tiles with a partly filled last row tile and a partly used
@@ -648,6 +650,12 @@ BITS_SHAPES = {
     # more than 8192 features with K = 2048 and 4096: o and down
     "wide_1l": WL.ModelShape("wide_1l", 303, L=1, Hd=8448, Hq=16, Hkv=2,
                              D=128, I=4096, V=512),
+    # q|k|v and gate/up above 8192 features, hidden 2048 and 4096: the
+    # persistent form of up to 32 rows on packed activations
+    "heads_2048": WL.ModelShape("heads_2048", 304, L=1, Hd=2048, Hq=64, Hkv=8,
+                                D=128, I=8256, V=512),
+    "heads_4096": WL.ModelShape("heads_4096", 305, L=1, Hd=4096, Hq=64, Hkv=8,
+                                D=128, I=512, V=512),
 }
 # rows: one 32-row block, two, four, the 2-D tiles (three row tiles, two,
 # four with 256-token SwiGLU tiles, a partly filled last one)
@@ -655,7 +663,8 @@ BITS_CASES = [("tiny2", 2, 16), ("tiny2", 5, 31), ("tiny2", 17, 16),
               ("qwen3_8b_1l", 1, 31), ("qwen3_8b_1l", 2, 24),
               ("qwen3_8b_1l", 6, 32), ("qwen3_8b_1l", 8, 32),
               ("qwen3_8b_1l", 13, 31), ("qwen3_8b_1l", 16, 32),
-              ("wide_1l", 1, 32)]
+              ("wide_1l", 1, 32), ("heads_2048", 1, 31),
+              ("heads_2048", 2, 16), ("heads_4096", 1, 32)]
 
 
 @functools.lru_cache(maxsize=1)
