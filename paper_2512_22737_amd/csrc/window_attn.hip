@@ -82,11 +82,12 @@ struct AttnArgs {
   // Workgroups take the sequences from the last one down (callers whose
   // later sequences have the longer prefixes: the longest start first)
   int rev;
+  float scale_log2;       // softmax_scale * log2(e)
   // by_len > 0: workgroups take the sequences by their prefix length, the
   // by_len longest first (they land one per CU), then the others so that the
-  // shortest share a CU with the longest (see sequence_by_length)
+  // shortest share a CU with the longest (see sequence_by_length).  Last, so
+  // that the kernels that do not read it keep their argument loads
   int by_len;
-  float scale_log2;       // softmax_scale * log2(e)
 };
 
 // Kernel shape for a given number of query rows per kv head.
