@@ -182,21 +182,31 @@ __device__ __forceinline__ int64_t win_row(const AttnArgs& a, int b, int qi) {
 }
 
 // Sequence validity; bad lengths are reported and the sequence skipped.
-__device__ __forceinline__ bool seq_ok(const AttnArgs& a, int b, int& c) {
-  c = a.plen[b];
+__device__ __forceinline__ bool len_ok(const AttnArgs& a, int c) {
   return c >= 0 && c <= a.max_prefix &&
          static_cast<int64_t>(c) <= static_cast<int64_t>(a.max_pages) * kPage;
 }
+
+// The workgroups go by length if some prefix is this long and some differs
+// from the first one's by this much
+constexpr int kByLenMin = 2048;
+constexpr int kByLenSpread = 512;
 
 // The sequence that slot (0 <= slot < B <= 64) takes when the workgroups go
 // by prefix length: slots 0 .. by_len-1 the longest, in falling order, then
 // the shortest in rising order if everything is resident at once (slot k and
 // slot by_len + k share a CU), else on in falling order.  One lane per
-// sequence; equal lengths keep their order, so every sequence has one slot.
-__device__ __forceinline__ int sequence_by_length(const AttnArgs& a, int slot) {
+// sequence (len: its prefix length); equal lengths keep their order, so every
+// sequence has one slot.  Short prefixes, and lengths that are near each
+// other, keep theirs too (the ranking takes about 0.6 us).
+__device__ __forceinline__ int sequence_by_length(const AttnArgs& a, int slot,
+                                                  int len) {
   const int lane = lane_id();
-  const int len = a.plen[min(lane, a.B - 1)];
-  if (ballot(len != __builtin_amdgcn_readfirstlane(len)) == 0) return slot;
+  const uint32_t off = static_cast<uint32_t>(len) -
+                       static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(len)) +
+                       kByLenSpread - 1;
+  if (ballot(len >= kByLenMin) == 0 || ballot(off > 2 * kByLenSpread - 2) == 0)
+    return slot;
   int rank = 0;
 #pragma unroll 4
   for (int j = 0; j < a.B; ++j) {
@@ -298,8 +308,14 @@ void window_attn_kernel(AttnArgs a) {
   wg /= a.qblocks;
   const int kvh = wg % a.Hkv;
   int b = a.rev ? a.B - 1 - wg / a.Hkv : wg / a.Hkv;
-  if (TWO && a.by_len > 0)
-    b = __builtin_amdgcn_readfirstlane(sequence_by_length(a, b));
+  int c = 0;
+  const bool by_len = TWO && a.by_len > 0;
+  if (by_len) {
+    // one round trip for the order and for this sequence's length
+    const int len = a.plen[min(lane_id(), a.B - 1)];
+    b = __builtin_amdgcn_readfirstlane(sequence_by_length(a, b, len));
+    c = __builtin_amdgcn_readlane(len, b);
+  }
 
   const int wave = threadIdx.x / kWave;
   const int lane = lane_id();
@@ -327,8 +343,8 @@ void window_attn_kernel(AttnArgs a) {
           bf16x8_t, *reinterpret_cast<const u16x8_t*>(qp + kk * 16 + hf * 8));
   }
 
-  int c;
-  if (!seq_ok(a, b, c)) {
+  if (!by_len) c = a.plen[b];
+  if (!len_ok(a, c)) {
     if (a.status && threadIdx.x == 0 && split == 0 && qb == 0 && kvh == 0)
       atomicOr(a.status + b, WEDLM_SEQ_BAD_LEN);
     return;
@@ -945,8 +961,8 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
       vs[i] = *reinterpret_cast<const u16x8_t*>(op + static_cast<int64_t>(s) * D);
     }
   }
-  int c;
-  if (!seq_ok(a, b, c)) return;                    // uniform over the row
+  const int c = a.plen[b];
+  if (!len_ok(a, c)) return;                       // uniform over the row
   const int nsplit_b = seq_split(c, a.nsplit).n;
   float M = kNegInf;
 #pragma unroll
@@ -1104,10 +1120,13 @@ int window_attn_impl(
   // two prefixes it holds, so they are paired by length, for up to one
   // sequence per lane.  Shuffled prefixes, 32/8 heads, W = 32, against taking
   // the sequences in order: 64 of 512 to 4096 145 -> 124 us, 48 of 100 to
-  // 5000 146 -> 127, 32 of 512 to 4096 (two splits) 90 -> 82; equal ones keep
-  // their order (64 of 2304 113.8 -> 113.8).  The ordering itself takes about
-  // 0.6 us, so prefixes of less than 1024 (a call of 25 us) go without.
-  if (p.two && pair_half == 0 && B > 1 && B <= kWave && max_prefix_len >= 1024)
+  // 5000 146 -> 127, 32 of 512 to 4096 (two splits) 90 -> 82.  Sorted
+  // ones (64 of 1 to 1500) lost 6%, those of 1 to 2000 in no order gain 1.5%,
+  // and prefixes within 5% of each other lost 1.2%: shorter than kByLenMin, by
+  // the caller's bound or, on the device, all of them, or within kByLenSpread
+  // of the first one they are taken in order.
+  if (p.two && pair_half == 0 && B > 1 && B <= kWave &&
+      max_prefix_len >= kByLenMin)
     a.by_len = std::max(1, 256 / (Hkv * p.qblocks * p.nsplit));
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
   if (p.nsplit > 1) {

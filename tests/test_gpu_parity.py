@@ -480,12 +480,18 @@ def test_attention_status_bits():
 
 # sequences taken by prefix length (two workgroups per CU): equal lengths,
 # empty prefixes, one that is out of range, all equal, a batch of more than
-# two rounds of CUs, and splits
+# two rounds of CUs, splits, and the least spread that is ordered
 @pytest.mark.parametrize("lens", [
     [0, 0, 5, 333, 333, 40, 16, 1040] * 4, [1024] * 32,
     [-1] + [1100 - 33 * i for i in range(31)],
     [31 * (i % 7) for i in range(63)] + [1025],
-    [2048 + 64 * (i % 3) for i in range(16)]])
+    [2048 + 64 * (i % 3) for i in range(16)],
+    # ordered where one reaches 2048 and one is 512 away from the first
+    [2048 + 700 * (i % 3) for i in range(16)],
+    [2100] * 31 + [1589], [2100] * 31 + [1588], [1535] + [2047] * 31,
+    [1536] + [2048] * 31, [0, 0, 5, 333, 333, 40, 16, 2080] * 4,
+    [-1] + [2100 - 66 * i for i in range(31)],
+    [62 * (i % 7) for i in range(63)] + [2049]])
 def test_sequences_by_length(lens):
     import torch
     from paper_2512_22737_amd import wedlm
@@ -503,7 +509,7 @@ def test_sequences_by_length(lens):
     kc, vc = bf(at, Hkv, 16, D), bf(at, Hkv, D, 16)
     q, k, v = bf(B, W, Hq, D), bf(B, W, Hkv, D), bf(B, W, Hkv, D)
     n = wedlm.wedlm_window_attn_workspace_size(B, W, Hq, Hkv, D, mp)
-    assert (n > 0) == (B == 16)                 # the last case splits
+    assert (n > 0) == (B == 16)                 # those cases split
     out = torch.zeros(B, W, Hq, D, dtype=torch.bfloat16, device="cuda")
     st = torch.zeros(B, dtype=torch.int32, device="cuda")
     wedlm.wedlm_window_attn(
