@@ -1448,7 +1448,7 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool xp, bool split_store) {
   GemmPlan p{};
   p.nb = gemm_nb(M, epi == kSwiglu);
   p.n_nb = N / 32;
-  p.n_rg = (M + 32 * p.nb - 1) / (32 * p.nb);
+  p.n_rg = (M - 1) / (32 * p.nb) + 1;
   p.n_ks = 1;
   p.nw = kGWaves;
   if (epi == kAddF32 && p.nb == 1 && K / kKStep <= 64) {
@@ -1460,8 +1460,9 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool xp, bool split_store) {
     p.nw = 4;
     p.n_ks = std::max(1, K / kKStep / (4 * 8));
   } else if (epi == kAddF32 || (epi == kStoreBf16 && split_store)) {
-    const int wgs = p.n_nb * p.n_rg;
-    p.n_ks = std::max(1, std::min(kGemmTargetWgs / wgs, K / kKStep / kGWaves));
+    const int64_t wgs = static_cast<int64_t>(p.n_nb) * p.n_rg;
+    p.n_ks = std::max(1, std::min(static_cast<int>(kGemmTargetWgs / wgs),
+                                  K / kKStep / kGWaves));
   }
   const int spw = K / kKStep / kGWaves;
   if (p.nb == 1 && p.n_nb > kGemmTargetWgs && K % (kKStep * kGWaves) == 0 &&
@@ -1575,7 +1576,7 @@ GemmPlan linear_plan(int M, int N, int K, int epi, size_t part_bytes) {
   p.two_d = true;
   const int S = K / kKStep;
   p.n_nb = N / 32;
-  p.n_tt = (M + 32 * k2dTok - 1) / (32 * k2dTok);
+  p.n_tt = (M - 1) / (32 * k2dTok) + 1;
   const size_t room = part_bytes / (static_cast<size_t>(M) * N * sizeof(float));
   // two waves per feature group need an even number of steps; one is for the
   // others and for SwiGLU.  A residual-add or stored product splits K (at
@@ -1585,8 +1586,10 @@ GemmPlan linear_plan(int M, int N, int K, int epi, size_t part_bytes) {
     if (wk == 2 ? S % 2 != 0 : S % 2 == 0 && epi != kSwiglu) continue;
     const int per = kGWaves / wk * (epi == kSwiglu ? 1 : 2);
     const int n_ft = (p.n_nb + per - 1) / per;
-    const int most = epi == kSwiglu
-                         ? 1 : std::min(kGemmTargetWgs / (n_ft * p.n_tt), S / 4);
+    const int64_t tiles = static_cast<int64_t>(n_ft) * p.n_tt;
+    const int most =
+        epi == kSwiglu
+            ? 1 : std::min(static_cast<int>(kGemmTargetWgs / tiles), S / 4);
     for (const int ks : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
       if (ks > 1 && (ks > most || static_cast<size_t>(ks) > room)) break;
       const double us = tiles_us(wk, n_ft, p.n_tt, ks, M, N, K);

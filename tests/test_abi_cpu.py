@@ -5,6 +5,8 @@ import ctypes
 import glob
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -75,6 +77,21 @@ def test_version_and_strerror():
 def test_linear_plan(M, N, K, epi, splits):
     assert _lib().wedlm_linear_workspace_size(M, N, K, epi) == \
         splits * M * N * 4
+
+
+# Tiles whose number does not fit 32 bits (2^32 of them, and rows near the
+# type's end): no split, and no division by their number's low half
+@pytest.mark.parametrize("M,N", [(1 << 24, 1 << 24), (1 << 30, 1 << 30),
+                                 (1 << 23, 1 << 23),
+                                 (2**31 - 1, 2**31 - 32)])
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_linear_workspace_of_huge_products(M, N, epi):
+    code = (f"import ctypes; f = ctypes.CDLL({LIB!r})"
+            ".wedlm_linear_workspace_size; f.restype = ctypes.c_size_t; "
+            f"print(f({M}, {N}, 64, {epi}))")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True,
+                       text=True, timeout=60)
+    assert (r.returncode, r.stdout.strip()) == (0, "0")
 
 
 def _fake():
