@@ -555,19 +555,21 @@ __global__ __launch_bounds__(NW * kWave) void gemm_kernel(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Up to 32 rows, K 4096 or 2048 and more feature blocks (for SwiGLU gate
-// blocks with their up blocks) than CUs: a persistent form of the kernel
-// above.  A workgroup loads its waves' activations once (SPW steps per wave,
-// 128 registers at 8) and walks several blocks; the weight loads run two steps
-// ahead across blocks, so the stream never stops for a block's sum, and the
-// activations are read from L2 once per workgroup instead of once per block
-// (row-major ones 64 bytes of 32 rows at a time).  The waves' sums of a block
-// meet in one of two LDS buffers, in wave order, with one barrier per block:
-// for stored and SwiGLU products the same bits as the plain form (which takes
-// residual adds of K up to 4096 in four waves and one or two splits).  Bound
-// by the weight stream: gate/up (201 MB) at 32 row-major rows 50 -> 41 us, at
-// 16 43 -> 38, at one 39 -> 36; a decoder step of one window, 8 layers, 1236
-// -> 1197 us with packed ones.
+// Up to 32 rows, an even number of K steps per wave up to eight (K 1024, 2048,
+// 3072 or 4096: the weights' two stages line up with the blocks, and eight
+// steps of activations are what the registers hold) and more feature blocks
+// (for SwiGLU gate blocks with their up blocks) than CUs: a persistent form of
+// the kernel above.  A workgroup loads its waves' activations once (SPW steps
+// per wave, 128 registers at 8) and walks several blocks; the weight loads run
+// two steps ahead across blocks, so the stream never stops for a block's sum,
+// and the activations are read from L2 once per workgroup instead of once per
+// block (row-major ones 64 bytes of 32 rows at a time).  The waves' sums of a
+// block meet in one of two LDS buffers, in wave order, with one barrier per
+// block: for stored and SwiGLU products the same bits as the plain form (which
+// takes residual adds of K up to 4096 in four waves and one or two splits).
+// Bound by the weight stream: gate/up (201 MB) at 32 row-major rows 50 -> 41
+// us, at 16 43 -> 38, at one 39 -> 36; a decoder step of one window, 8 layers,
+// 1236 -> 1197 us with packed ones.
 // (K split three ways, down at one row took 23 us against 21.)
 // ---------------------------------------------------------------------------
 template <int NA, int SPW, int EPI, bool XP>
@@ -1023,11 +1025,11 @@ __global__ __launch_bounds__(kGThreads) void gemm2d_packed_wide_kernel(
 
 // ---------------------------------------------------------------------------
 // 2-D tiled GEMM for many rows of row-major activations (wedlm_linear).  A
-// workgroup of eight waves computes FG feature groups x 128 tokens (4 row tiles) over its run of K steps; a
-// feature group is two 32-feature blocks (for SwiGLU a gate block and its up
-// block) and belongs to one wave (WK = 1: eight groups, 512 features) or to
-// two (WK = 2: four groups, 256 features), which then take alternate k steps
-// and add their sums through LDS at the end.
+// workgroup of eight waves computes FG feature groups x 128 tokens (4 row
+// tiles) over its run of K steps; a feature group is two 32-feature blocks
+// (for SwiGLU a gate block and its up block) and belongs to one wave (WK = 1:
+// eight groups, 512 features) or to two (WK = 2: four groups, 256 features),
+// which then take alternate k steps and add their sums through LDS at the end.
 //   MFMA         v_mfma_f32_16x16x32_bf16: per multiply-add it reads and
 //                writes half the accumulators of the 32x32x16 form, and under
 //                the package power limit it runs 17% faster (a register-only
@@ -1423,8 +1425,8 @@ constexpr int kWideMinWgs = 3 * kGemmTargetWgs / 4;
 // them, where the plain form keeps two workgroups on a CU.  It loses where
 // its rounds are few and full and there are few activations to read again.
 // Measured (plain against persistent), N 8224 to 32768, 1 to 32 rows:
-//   stored products   faster throughout (K 2048 at one row, N 16384 15.4 and
-//                     15.0 us)
+//   stored products   K 4096 and 2048 faster throughout (K 2048 at one row, N
+//                     16384 15.4 and 15.0 us)
 //   residual adds     K 4096 faster throughout; K 2048 at one row N 10240
 //                     11.3 and 10.8, N 16384 13.4 and 15.3.  The decoder's
 //                     (hidden above 8192) keep the plain form, whose sums go
@@ -1435,11 +1437,19 @@ constexpr int kWideMinWgs = 3 * kGemmTargetWgs / 4;
 //   SwiGLU, row-major 4096 x 16384 at one row 45.4 and 47.6, at 32 rows 52.8
 //                     and 51.1; 2048 x 14336 at one row 22.9 and 23.9; 4096 x
 //                     12288 39.0 and 36.6
+//   K 1024 and 3072   two and three full rounds lose or are even at few rows
+//                     (N 16384 at one row 3072 stored 18.0 and 19.0, 1024
+//                     added 8.4 and 9.1); 9216 at one row 15.3 and 13.9, 7.5
+//                     and 6.8, at 24 rows 21.6 and 16.4, 11.1 and 7.7.
+//                     Packed: gate/up 9216 x 3072 takes 6 us less per layer,
+//                     16384 the same
 bool persistent_pays(int M, int n_nb, int rounds, int spw, int epi, bool xp) {
   const double fill = static_cast<double>(n_nb) / (rounds * kGemmTargetWgs);
-  if (epi == kStoreBf16) return true;
-  if (epi == kAddF32) return !xp && (spw == 8 || M >= 20 || fill <= 0.67);
-  if (xp) return rounds > 2 || fill <= 0.9;
+  const bool own_rule = spw == 4 || spw == 8;     // K 2048 and 4096
+  if (epi == kStoreBf16 && own_rule) return true;
+  if (xp) return epi != kAddF32 && (rounds > 2 || fill <= 0.9);
+  if (epi == kAddF32 && own_rule)
+    return spw == 8 || M >= 20 || fill <= 0.67;
   return M >= 24 || fill <= 0.8 || rounds >= 4 || (rounds == 3 && spw == 8);
 }
 
@@ -1466,7 +1476,7 @@ GemmPlan rows_plan(int M, int N, int K, int epi, bool xp, bool split_store) {
   }
   const int spw = K / kKStep / kGWaves;
   if (p.nb == 1 && p.n_nb > kGemmTargetWgs && K % (kKStep * kGWaves) == 0 &&
-      (spw == 8 || spw == 4)) {
+      spw % 2 == 0 && spw <= 8) {
     const int rounds = (p.n_nb + kGemmTargetWgs - 1) / kGemmTargetWgs;
     if (persistent_pays(M, p.n_nb, rounds, spw, epi, xp)) {
       p.spw = spw;
@@ -1687,10 +1697,13 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
     return WEDLM_E_SHAPE;
   const int nb = p.nb;
   if (p.spw > 0) {
-    if (p.spw == 8 && xp) persistent_launch<8, true>(a, epi, p.wgs, st);
-    else if (p.spw == 8) persistent_launch<8, false>(a, epi, p.wgs, st);
-    else if (xp) persistent_launch<4, true>(a, epi, p.wgs, st);
-    else persistent_launch<4, false>(a, epi, p.wgs, st);
+    using Launch = void (*)(const GemmArgs&, int, int, hipStream_t);
+    constexpr Launch by_pairs[2][4] = {
+        {persistent_launch<2, false>, persistent_launch<4, false>,
+         persistent_launch<6, false>, persistent_launch<8, false>},
+        {persistent_launch<2, true>, persistent_launch<4, true>,
+         persistent_launch<6, true>, persistent_launch<8, true>}};
+    by_pairs[xp][p.spw / 2 - 1](a, epi, p.wgs, st);
   } else if (epi == kSwiglu) {
     if (nb == 1) gemm_launch<1, 2, 2, kSwiglu>(a, xp, st);
     else gemm_launch<2, 2, 2, kSwiglu>(a, xp, st);

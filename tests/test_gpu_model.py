@@ -249,11 +249,12 @@ def test_linear_2d(M, N, K, epi):
 
 
 # the persistent form of up to 32 rows: more 32-feature blocks than CUs (257:
-# one workgroup with a block fewer than the others; 520: three rounds), four
-# and eight steps per wave, one row, a ragged and a full row block
+# one workgroup with a block fewer than the others; 520: three rounds), two,
+# four, six and eight steps per wave, one row, a ragged and a full row block
 @pytest.mark.parametrize("M,N,K,epi", [
     (1, 257 * 32, 2048, 2), (32, 257 * 32, 4096, 2), (31, 520 * 32, 2048, 1),
-    (17, 300 * 32, 4096, 0)])
+    (17, 300 * 32, 4096, 0), (1, 257 * 32, 3072, 2), (32, 520 * 32, 1024, 1),
+    (31, 300 * 32, 3072, 1), (17, 800 * 32, 1024, 0)])
 def test_linear_persistent(M, N, K, epi):
     test_linear(M, N, K, epi)
 
@@ -261,13 +262,15 @@ def test_linear_persistent(M, N, K, epi):
 # the bits of a feature do not depend on how many are computed: up to 8192 of
 # them (4096 with their up rows) the plain form runs.  Residual adds alone
 # differ where the persistent form takes them, which it does not from the
-# row and block counts on at which it is the slower one (at K 2048)
+# row and block counts on at which it is the slower one (at K 1024 to 3072)
 @pytest.mark.parametrize("M,N,K,epi,same", [
     (1, 8224, 4096, 0, True), (32, 12320, 2048, 0, True),
     (1, 8224, 2048, 2, True), (31, 12288, 4096, 2, True),
     (9, 16384, 4096, 2, True), (32, 12288, 2048, 1, False),
     (1, 12288, 2048, 1, True), (19, 16384, 2048, 1, True),
-    (1, 12288, 4096, 1, False)])
+    (1, 12288, 4096, 1, False), (1, 12288, 1024, 2, True),
+    (31, 9216, 3072, 0, True), (16, 16384, 3072, 2, True),
+    (1, 12288, 3072, 1, False), (23, 16384, 1024, 1, True)])
 def test_linear_same_bits_as_the_plain_form(M, N, K, epi, same):
     w = W_()
     g = torch.Generator(device=DEV).manual_seed(N + K + M)
@@ -650,8 +653,12 @@ BITS_SHAPES = {
     # more than 8192 features with K = 2048 and 4096: o and down
     "wide_1l": WL.ModelShape("wide_1l", 303, L=1, Hd=8448, Hq=16, Hkv=2,
                              D=128, I=4096, V=512),
-    # q|k|v and gate/up above 8192 features, hidden 2048 and 4096: the
+    # q|k|v and gate/up above 8192 features, hidden 1024 to 4096: the
     # persistent form of up to 32 rows on packed activations
+    "heads_1024": WL.ModelShape("heads_1024", 306, L=1, Hd=1024, Hq=64, Hkv=8,
+                                D=128, I=8256, V=512),
+    "heads_3072": WL.ModelShape("heads_3072", 307, L=1, Hd=3072, Hq=64, Hkv=8,
+                                D=128, I=8256, V=512),
     "heads_2048": WL.ModelShape("heads_2048", 304, L=1, Hd=2048, Hq=64, Hkv=8,
                                 D=128, I=8256, V=512),
     "heads_4096": WL.ModelShape("heads_4096", 305, L=1, Hd=4096, Hq=64, Hkv=8,
@@ -664,7 +671,8 @@ BITS_CASES = [("tiny2", 2, 16), ("tiny2", 5, 31), ("tiny2", 17, 16),
               ("qwen3_8b_1l", 6, 32), ("qwen3_8b_1l", 8, 32),
               ("qwen3_8b_1l", 13, 31), ("qwen3_8b_1l", 16, 32),
               ("wide_1l", 1, 32), ("heads_2048", 1, 31),
-              ("heads_2048", 2, 16), ("heads_4096", 1, 32)]
+              ("heads_2048", 2, 16), ("heads_4096", 1, 32),
+              ("heads_1024", 1, 32), ("heads_3072", 1, 31)]
 
 
 @functools.lru_cache(maxsize=1)
