@@ -1537,10 +1537,14 @@ GemmPlan packed_plan(int M, int N, int K, int epi, bool split_store) {
 
 // The split-K kernel: S / (8 n_ks) steps per wave and round, by its rows per
 // group (the rows of a partly filled last group re-read one row) and weight
-// blocks.
+// blocks.  A round that only begins costs less than a full one: not all XCDs
+// have it, and two workgroups fit a CU.
 double rows_us(const GemmPlan& p, int M, int N, int K, int epi) {
   const double full = (p.n_nb + 7) / 8 * static_cast<double>(p.n_rg) * p.n_ks / 32;
-  const double rounds = full <= 1 ? 1 : 0.2 * full + 0.8 * std::ceil(full);
+  const double begun = full - std::floor(full);
+  const double rounds =
+      full <= 1 ? 1
+                : 0.2 * full + 0.8 * (full - begun + std::min(1.0, 4 * begun));
   const double steps = static_cast<double>(K) / kKStep / (p.nw * p.n_ks);
   const double fill = std::min(1.0, full);
   const double per_step = p.nb == 4        ? 3.9 + 0.85 * fill
@@ -1566,9 +1570,15 @@ double tiles_us(int wk, int n_ft, int n_tt, int n_ks, int M, int N, int K) {
 }
 
 // Row-major activations of more than 32 rows take the 2-D kernel where its
-// estimate is 6% below the split-K kernel's.  Of the 2324 products 922 do;
-// six of them are more than 2% slower than with the split-K kernel, at most
-// 6%, and over all the choice is 0.7% from the fastest.  Both sides measured
+// estimate is 10% below the split-K kernel's; stored products and residual
+// adds with one wave per feature group (an odd number of steps) count 2 us
+// more, as their times scatter most.  On 9000 products that no constant was
+// chosen on (33 to 1024 rows, N 128 to 12288, K 256 to 12288) 2866 take it, in
+// 0.39 of the split-K kernel's time; five of them are more than 2% slower, at
+// most 6% (339 x 2464 x 8320 SwiGLU 90 and 96 us).  With full rounds for those
+// that only begin, at 6% and without the 2 us, 3291 of 9000 took it, 23 of
+// them more than 2% slower and five more than 10% (260 x 448 x 8896 added 21.1
+// and 25.7), for 0.9% more of the time saved.  Both sides measured elsewhere
 // (split-K against 2-D): down (4096 x 12288) at 512 rows 240 and 63 us, at 64
 // rows 49 and 33; gate/up (12288 x 4096) at 128 rows 104 and 66; o (4096 x
 // 4096) at 40 rows 17.8 and 19.5, at 128 rows 35.6 and 23.0; 1024 x 1024 at
@@ -1580,7 +1590,7 @@ GemmPlan linear_plan(int M, int N, int K, int epi, size_t part_bytes) {
   const GemmPlan rows = rows_plan(M, N, K, epi, false, false);
   // (a group's rows are read through a 32-bit buffer resource)
   if (M <= 32 || K > (1 << 22)) return rows;
-  double best = 0.94 * rows_us(rows, M, N, K, epi);
+  double best = 0.9 * rows_us(rows, M, N, K, epi);
   if (best <= k2dStart + k2dRound) return rows;
   GemmPlan p{};
   p.two_d = true;
@@ -1602,7 +1612,8 @@ GemmPlan linear_plan(int M, int N, int K, int epi, size_t part_bytes) {
             ? 1 : std::min(static_cast<int>(kGemmTargetWgs / tiles), S / 4);
     for (const int ks : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
       if (ks > 1 && (ks > most || static_cast<size_t>(ks) > room)) break;
-      const double us = tiles_us(wk, n_ft, p.n_tt, ks, M, N, K);
+      const double us = tiles_us(wk, n_ft, p.n_tt, ks, M, N, K) +
+                        (wk == 1 && epi != kSwiglu ? 2.0 : 0.0);
       if (us >= best) continue;
       best = us;
       p.wk = wk;
@@ -1653,11 +1664,12 @@ int gemm(const uint16_t* x, const uint16_t* w, int M, int N, int K, void* out,
       return reinterpret_cast<uintptr_t>(q) % n == 0;
     };
     p = linear_plan(M, N, K, epi, part && aligned(part, 16) ? part_bytes : 0);
-    const GemmPlan r = rows_plan(M, N, K, epi, false, false);
-    if (p.two_d && (r.part_bytes > (part ? part_bytes : 0) ||
-                    !aligned(x, 16) || ldo % 4 != 0 ||
-                    !aligned(out, epi == kAddF32 ? 16 : 8)))
-      p = r;
+    if (p.two_d) {
+      const GemmPlan r = rows_plan(M, N, K, epi, false, false);
+      if (r.part_bytes > (part ? part_bytes : 0) || !aligned(x, 16) ||
+          ldo % 4 != 0 || !aligned(out, epi == kAddF32 ? 16 : 8))
+        p = r;
+    }
   }
   if (p.part_bytes > 0 && (!part || part_bytes < p.part_bytes))
     return WEDLM_E_WORKSPACE;

@@ -71,6 +71,9 @@ def test_version_and_strerror():
     (512, 4096, 12288, 1, 4),       # 250, 61
     (64, 4096, 12288, 0, 16),       # 81, 33
     (1024, 1024, 1024, 0, 0),       # either way
+    (260, 448, 8896, 1, 6),         # 21.1, 25.7 (16)
+    (250, 1856, 2624, 0, 0),        # 23.9, 26.8 (10)
+    (513, 928, 5632, 2, 0),         # 47, 55
     (32, 4096, 12288, 1, 2),        # up to 32 rows: split-K
     (32, 4096, 12288, 0, 0),
 ])

@@ -216,17 +216,20 @@ LINEAR_2D_CASES = [
     (257, 4128, 2048, 2), (1000, 4128, 1088, 1), (1000, 4128, 1088, 0),
     (513, 4096, 256, 0), (64, 1056, 4096, 0),
     # two waves per group: 2; 2 and 3; 3 and 4; 4 and 5; 5 and 6 stages
-    (33, 32, 4096, 0), (200, 32, 1664, 0), (1000, 1056, 1280, 1),
+    (33, 32, 4096, 0), (1000, 32, 2816, 1), (1000, 1056, 1280, 1),
     (33, 6176, 6144, 0), (130, 4128, 4096, 1),
     # 2 and 3 stages, not split
     (200, 6176, 256, 2), (257, 6176, 384, 1),
-    # one wave per group: 4 and 5; 5 and 6; 6 and 7 stages; 4 and 7, not split
-    (96, 32, 2624, 0), (64, 4128, 4160, 1), (257, 4128, 1728, 0),
+    # one wave per group: 4 and 5; 5 and 6; 6 and 7; 4 and 5 stages; 4 and 7,
+    # not split
+    (64, 4128, 4672, 1), (40, 4128, 6080, 1), (33, 4128, 6848, 1),
+    (257, 4128, 1728, 0), (257, 4128, 1728, 1),
     (513, 6176, 256, 2), (300, 6176, 448, 2),
     # fewer splits than the split-K kernel would take (and want room for)
-    (280, 32, 11392, 1),
+    (1000, 32, 11648, 1),
     # beside the line: these stay with the split-K kernel
     (130, 2080, 2048, 0), (130, 2080, 2048, 1), (300, 4128, 1088, 2),
+    (200, 32, 1664, 0), (96, 32, 2624, 0), (64, 4128, 4160, 1),
 ]
 
 
@@ -244,7 +247,7 @@ def test_linear_2d(M, N, K, epi):
     odd = torch.zeros(M, N + 1, dtype=dt, device=DEV)
     w.wedlm_linear(x, wd, epi, even)
     w.wedlm_linear(x, wd, epi, odd)
-    two_d = (M, N, K, epi) not in LINEAR_2D_CASES[-3:]
+    two_d = (M, N, K, epi) not in LINEAR_2D_CASES[-6:]
     assert torch.equal(even, odd[:, :N]) == (not two_d)
 
 
