@@ -187,18 +187,33 @@ __device__ __forceinline__ bool len_ok(const AttnArgs& a, int c) {
          static_cast<int64_t>(c) <= static_cast<int64_t>(a.max_pages) * kPage;
 }
 
-// The workgroups go by length if some prefix is this long and some differs
-// from the first one's by this much
+// The workgroups go by length if some prefix is this long, some differs from
+// the first one's by this much, and the CU with the most positions would have
+// this many more per split than the best order can leave it
 constexpr int kByLenMin = 2048;
 constexpr int kByLenSpread = 512;
+constexpr int kByLenGain = 256;
+
+// Largest of a value over the wave's lanes: rows of 16 lanes shifted by 1, 2,
+// 4 and 8, then lane 15 of each row to the next row and lane 31 to the upper
+// half, so that lane 63 has it.
+template <int CTRL>
+__device__ __forceinline__ int dpp_max(int v) {
+  return max(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ int wave_max(int v) {
+  v = dpp_max<0x118>(dpp_max<0x114>(dpp_max<0x112>(dpp_max<0x111>(v))));
+  return __builtin_amdgcn_readlane(dpp_max<0x143>(dpp_max<0x142>(v)), 63);
+}
 
 // The sequence that slot (0 <= slot < B <= 64) takes when the workgroups go
 // by prefix length: slots 0 .. by_len-1 the longest, in falling order, then
 // the shortest in rising order if everything is resident at once (slot k and
 // slot by_len + k share a CU), else on in falling order.  One lane per
 // sequence (len: its prefix length); equal lengths keep their order, so every
-// sequence has one slot.  Short prefixes, and lengths that are near each
-// other, keep theirs too (the ranking takes about 0.6 us).
+// sequence has one slot.  Short prefixes, lengths that are near each other
+// and those whose order leaves the fullest CU as it is (one long sequence
+// among short ones) keep theirs too: the ranking takes 1 to 3 us.
 __device__ __forceinline__ int sequence_by_length(const AttnArgs& a, int slot,
                                                   int len) {
   const int lane = lane_id();
@@ -206,6 +221,24 @@ __device__ __forceinline__ int sequence_by_length(const AttnArgs& a, int slot,
                        static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(len)) +
                        kByLenSpread - 1;
   if (ballot(len >= kByLenMin) == 0 || ballot(off > 2 * kByLenSpread - 2) == 0)
+    return slot;
+  const int l0 = min(max(len, 0), 1 << 24);
+  // more sequences than are resident, in falling order already
+  const int next = __shfl(l0, lane + 1);
+  if (a.B > 2 * a.by_len && ballot(lane + 1 < a.B && next > l0) == 0)
+    return slot;
+  // positions that lane's CU has with the sequences in their own order (lanes
+  // up to by_len; the others' sums are parts of those), against the longest
+  // with the shortest on its CU.  (Lengths out of range are clamped, so that
+  // the sums fit)
+  int sum = l0, more = 0;
+  for (int j = a.by_len; j < a.B; j += a.by_len) {
+    const int l = __shfl(l0, lane + j);
+    sum += lane + j < a.B ? l : 0;
+    ++more;
+  }
+  if (wave_max(sum) - wave_max(l0) + more * wave_max(-l0) <=
+      kByLenGain * a.nsplit)
     return slot;
   int rank = 0;
 #pragma unroll 4
@@ -1124,7 +1157,12 @@ int window_attn_impl(
   // ones (64 of 1 to 1500) lost 6%, those of 1 to 2000 in no order gain 1.5%,
   // and prefixes within 5% of each other lost 1.2%: shorter than kByLenMin, by
   // the caller's bound or, on the device, all of them, or within kByLenSpread
-  // of the first one they are taken in order.
+  // of the first one they are taken in order.  So are those that an order
+  // leaves on the same CUs by kByLenGain (one prefix of 2048 among 63 of 256,
+  // 8/2 heads and four splits, 29.4 -> 32.0 us with an order and 29.6 with the
+  // question alone; one of 4096 among 512 93.3 -> 97.6 and 93.5): from 374
+  // positions on, 28 shapes gained up to 21% or lost up to 3%, the latter by
+  // an order that they had already.
   if (p.two && pair_half == 0 && B > 1 && B <= kWave &&
       max_prefix_len >= kByLenMin)
     a.by_len = std::max(1, 256 / (Hkv * p.qblocks * p.nsplit));

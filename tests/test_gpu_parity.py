@@ -491,7 +491,15 @@ def test_attention_status_bits():
     [2100] * 31 + [1589], [2100] * 31 + [1588], [1535] + [2047] * 31,
     [1536] + [2048] * 31, [0, 0, 5, 333, 333, 40, 16, 2080] * 4,
     [-1] + [2100 - 66 * i for i in range(31)],
-    [62 * (i % 7) for i in range(63)] + [2049]])
+    [62 * (i % 7) for i in range(63)] + [2049],
+    # one long sequence among short ones keeps its place; the fullest CU has
+    # 256 and 257 positions more than an order leaves it
+    [256] * 31 + [2304], [2304] + [256] * 63, [300] * 9 + [5000] + [300] * 6,
+    [2048] + [256] * 15 + [512] + [256] * 15,
+    [2048] + [256] * 15 + [513] + [256] * 15,
+    # more than are resident: in falling order, and all but one
+    [2500 - 70 * i for i in range(33)],
+    [2500 - 70 * (i ^ 1) for i in range(33)]])
 def test_sequences_by_length(lens):
     import torch
     from paper_2512_22737_amd import wedlm
